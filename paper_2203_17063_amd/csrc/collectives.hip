@@ -8,6 +8,7 @@
 // workgroups that copy or reduce data (which all evaluate the decision for
 // the ranks they touch) never race with the workgroup that records it.
 #include <algorithm>
+#include <type_traits>
 
 #include "ecc_common.h"
 
@@ -78,118 +79,272 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble(
 }
 
 // Partial allreduce: workgroup 0 records the step; every other workgroup owns
-// kReduceThreads * kReduceElems consecutive elements and, for p = 0..P-1 in
-// order, takes the fresh contribution of eff ranks (writing it to the rank's
-// slot) or the slot of the others, summing in rank order.  A contribution
-// that its producer wrote into the slot itself (fresh[p] == slots[p]) is
-// read there and not written back.
-__global__ __launch_bounds__(kReduceThreads) void k_allreduce(
+// NTH * VP * W consecutive elements and, for p = 0..P-1 in order, takes the
+// fresh contribution of eff ranks (writing it to the rank's slot) or the slot
+// of the others, summing in rank order.  A contribution that its producer
+// wrote into the slot itself (fresh[p] == slots[p]) is read there and not
+// written back.  Memory-bound: 8 m (P + taken + 1) bytes, one add per element
+// read.
+//
+// Each workgroup stages its ranks' source and slot addresses in LDS once, so
+// that the loads of U ranks go out together with no pointer chase between
+// them, and W = 2 moves 16 bytes per lane at any 8-byte alignment (gfx950
+// takes such accesses unaligned).  The last pair of an odd vector is moved
+// back by one element: two lanes then handle the same element with the same
+// values.
+//
+// Loads and stores retire through one in-order counter, so the first load
+// awaited after a batch's slot stores waits for those stores.  SPLIT takes
+// the stores out of the chain: the grid's first workgroups only sum (eff
+// ranks are read from fresh, which the slots will equal), further workgroups
+// copy fresh to slot, 4 vectors per thread, and no workgroup reads what
+// another writes.
+struct ReduceArgs {
+    int32_t P, S;
+    int64_t t;
+    const uint8_t *arrived;
+    const int32_t *ver_in;
+    int32_t *ver_out;
+    int32_t *age_state;
+    uint8_t *eff_state;
+    unsigned long long *forced;
+    uint8_t *eff_user;
+    int32_t *result_clock;
+    int64_t m;
+    const double *const *fresh;
+    double *const *slots;
+    double *result;
+    int64_t n_sum;  // workgroups that sum (SPLIT: followed by those that copy)
+};
+
+constexpr int kReduceCopies = 4;   // SPLIT: vectors one thread of a copying workgroup moves
+constexpr int kReduceStage = 256;  // ranks staged in LDS at a time
+
+template <int NTH, int W, int VP, int U, bool SPLIT>
+__global__ __launch_bounds__(NTH) void k_allreduce(ReduceArgs a) {
+    using T = typename WordVec<W>::t;
+    __shared__ uint64_t s_src[kReduceStage], s_dst[kReduceStage];
+    const int tid = threadIdx.x;
+    const int64_t m = a.m;
+    if (blockIdx.x == 0) {
+        record_step(a.P, a.S, a.t, a.arrived, a.ver_in, a.ver_out, a.age_state, a.eff_state,
+                    a.forced, a.eff_user, nullptr, a.result_clock);
+        return;
+    }
+    if constexpr (SPLIT) {
+        if ((int64_t)blockIdx.x > a.n_sum) {
+            constexpr int64_t chunk = (int64_t)NTH * W * kReduceCopies;
+            const uint32_t chunks = (uint32_t)((m + chunk - 1) / chunk);
+            const uint32_t b = (uint32_t)(blockIdx.x - 1 - a.n_sum);
+            const int32_t p = (int32_t)(b / chunks);
+            if (!stale_select(a.ver_in[p], a.arrived[p], a.t, a.S)) return;
+            const double *src = a.fresh[p];
+            double *dst = a.slots[p];
+            if (src == dst) return;
+            const int64_t e0 = (int64_t)(b % chunks) * chunk + (int64_t)tid * W;
+            T v[kReduceCopies];
+#pragma unroll
+            for (int j = 0; j < kReduceCopies; ++j)
+                v[j] = *(GlobalPtr<const T>)(src + min(e0 + (int64_t)j * NTH * W, m - W));
+#pragma unroll
+            for (int j = 0; j < kReduceCopies; ++j) {
+                const int64_t e = e0 + (int64_t)j * NTH * W;
+                if (e < m) *(GlobalPtr<T>)(dst + min(e, m - W)) = v[j];
+            }
+            return;
+        }
+    }
+    const int64_t base = (int64_t)(blockIdx.x - 1) * (NTH * VP * W);
+    int64_t at[VP];
+    bool in[VP];
+    T acc[VP];
+#pragma unroll
+    for (int j = 0; j < VP; ++j) {
+        const int64_t e = base + ((int64_t)j * NTH + tid) * W;
+        in[j] = e < m;
+        at[j] = min(e, m - W);  // lanes past the end read the last vector
+        acc[j] = T(0.0);
+    }
+    for (int32_t c0 = 0; c0 < a.P; c0 += kReduceStage) {
+        const int32_t nc = min(kReduceStage, a.P - c0);
+        if (c0) __syncthreads();
+        for (int32_t k = tid; k < nc; k += NTH) {
+            const int32_t p = c0 + k;
+            const bool e = stale_select(a.ver_in[p], a.arrived[p], a.t, a.S);
+            const double *f = a.fresh[p];
+            double *s = a.slots[p];
+            s_src[k] = (uint64_t)(e ? f : s);
+            s_dst[k] = (!SPLIT && e && f != s) ? (uint64_t)s : 0;
+        }
+        __syncthreads();
+        // one batch of up to U ranks: every load, then the stores and the sums
+        auto batch = [&](int32_t k0, auto whole) {
+            T v[U][VP];
+            uint64_t src[U], dst[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int32_t k = whole ? k0 + u : min(k0 + u, nc - 1);
+                src[u] = s_src[k];
+                if constexpr (!SPLIT) dst[u] = s_dst[k];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                src[u] = wave_uniform(src[u]);
+                if constexpr (!SPLIT) dst[u] = wave_uniform(dst[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (whole || k0 + u < nc) {
+#pragma unroll
+                    for (int j = 0; j < VP; ++j)
+                        v[u][j] = *(GlobalPtr<const T>)((const double *)src[u] + at[j]);
+                }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (whole || k0 + u < nc) {
+                    if constexpr (!SPLIT) {
+                        if (dst[u]) {
+#pragma unroll
+                            for (int j = 0; j < VP; ++j)
+                                if (in[j]) *(GlobalPtr<T>)((double *)dst[u] + at[j]) = v[u][j];
+                        }
+                    }
+#pragma unroll
+                    for (int j = 0; j < VP; ++j)
+                        acc[j] = (u == 0 && c0 + k0 == 0) ? v[u][j] : acc[j] + v[u][j];
+                }
+        };
+        int32_t k = 0;
+        for (; k + U <= nc; k += U) batch(k, std::true_type{});
+        if (k < nc) batch(k, std::false_type{});
+    }
+#pragma unroll
+    for (int j = 0; j < VP; ++j)
+        if (in[j]) *(GlobalPtr<T>)(a.result + at[j]) = acc[j];
+}
+
+// The same for the longest vectors of many ranks: 1,024 threads own 16,384
+// elements (8 pairs per thread), and one rank's loads are in flight at a
+// time, its addresses and decision read per rank.  At this size the memory
+// sets the pace, and it runs best when all workgroups stream the same rank's
+// vector together: staging the addresses in LDS (2,837 against 2,806 us, 256
+// x 4M), two ranks in flight, or loading the next rank before this one's sums
+// (2,832) were slower, as were all narrower chunks (2,860 to 3,240).
+constexpr int kWideThreads = 1024;
+constexpr int kWidePairs = 8;
+
+__global__ __launch_bounds__(kWideThreads) void k_allreduce_wide(
     int32_t P, int32_t S, int64_t t, const uint8_t *__restrict__ arrived,
     const int32_t *__restrict__ ver_in, int32_t *__restrict__ ver_out,
     int32_t *__restrict__ age_state, uint8_t *__restrict__ eff_state,
     unsigned long long *__restrict__ forced, uint8_t *__restrict__ eff_user,
     int32_t *__restrict__ result_clock, int64_t m, const double *const *__restrict__ fresh,
     double *const *__restrict__ slots, double *__restrict__ result) {
+    using T = typename WordVec<2>::t;
     if (blockIdx.x == 0) {
         record_step(P, S, t, arrived, ver_in, ver_out, age_state, eff_state, forced, eff_user,
                     nullptr, result_clock);
         return;
     }
-    const int tid = threadIdx.x;
-    // 16-byte path only if every pointer involved is 16-byte aligned.
-    int ok = (((uintptr_t)result & 15) == 0) && ((m & 1) == 0);
-    for (int32_t p = tid; p < P; p += kReduceThreads)
-        ok = ok && ((((uintptr_t)fresh[p] | (uintptr_t)slots[p]) & 15) == 0);
-    const int vec = __syncthreads_and(ok);
-
-    const int64_t base = (int64_t)(blockIdx.x - 1) * (kReduceThreads * kReduceElems);
-    constexpr int U = kReduceU;
-    constexpr int VP = kReduceElems / 2;  // 16-byte pairs per thread
-    static_assert(kReduceElems % 2 == 0, "pairs of elements");
-    if (vec) {
-        // element pairs q[j] = chunk pair offset + tid + j * kReduceThreads
-        int64_t q[VP];
-        bool in[VP];
-        double2 acc[VP];
+    const int64_t base = (int64_t)(blockIdx.x - 1) * (kWideThreads * kWidePairs * 2);
+    int64_t at[kWidePairs];
+    bool in[kWidePairs];
+    T acc[kWidePairs];
 #pragma unroll
-        for (int j = 0; j < VP; ++j) {
-            q[j] = base / 2 + tid + (int64_t)j * kReduceThreads;
-            in[j] = 2 * q[j] < m;
-            acc[j] = make_double2(0.0, 0.0);
-        }
-        for (int32_t p0 = 0; p0 < P; p0 += U) {
-            double2 v[U][VP];
-            bool e[U], wr[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int32_t p = p0 + u;
-                if (p < P) {
-                    e[u] = stale_select(ver_in[p], arrived[p], t, S);
-                    const double *fp = fresh[p], *sp = slots[p];
-                    wr[u] = e[u] && fp != sp;
-                    const double2 *src = reinterpret_cast<const double2 *>(e[u] ? fp : sp);
-#pragma unroll
-                    for (int j = 0; j < VP; ++j)
-                        if (in[j]) v[u][j] = src[q[j]];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int32_t p = p0 + u;
-                if (p < P) {
-                    if (wr[u]) {
-                        double2 *dst = reinterpret_cast<double2 *>(slots[p]);
-#pragma unroll
-                        for (int j = 0; j < VP; ++j) {
-                            if (in[j]) dst[q[j]] = v[u][j];
-                        }
-                    }
-#pragma unroll
-                    for (int j = 0; j < VP; ++j) {
-                        if (p == 0) {
-                            acc[j] = v[u][j];
-                        } else {
-                            acc[j].x = acc[j].x + v[u][j].x;
-                            acc[j].y = acc[j].y + v[u][j].y;
-                        }
-                    }
-                }
-            }
-        }
-        double2 *r2 = reinterpret_cast<double2 *>(result);
-#pragma unroll
-        for (int j = 0; j < VP; ++j)
-            if (in[j]) r2[q[j]] = acc[j];
-    } else {
-        int64_t idx[kReduceElems];
-        double acc[kReduceElems];
-#pragma unroll
-        for (int j = 0; j < kReduceElems; ++j) {
-            idx[j] = base + tid + (int64_t)j * kReduceThreads;
-            acc[j] = 0.0;
-        }
-        for (int32_t p = 0; p < P; ++p) {
-            const bool e = stale_select(ver_in[p], arrived[p], t, S);
-            const double *fp = fresh[p];
-            double *sp = slots[p];
-            const bool wr = e && fp != sp;
-            const double *src = e ? fp : sp;
-            double v[kReduceElems];
-#pragma unroll
-            for (int j = 0; j < kReduceElems; ++j)
-                if (idx[j] < m) v[j] = src[idx[j]];
-#pragma unroll
-            for (int j = 0; j < kReduceElems; ++j) {
-                if (idx[j] < m) {
-                    if (wr) sp[idx[j]] = v[j];
-                    acc[j] = (p == 0) ? v[j] : acc[j] + v[j];
-                }
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < kReduceElems; ++j)
-            if (idx[j] < m) result[idx[j]] = acc[j];
+    for (int j = 0; j < kWidePairs; ++j) {
+        const int64_t e = base + 2 * ((int64_t)threadIdx.x + (int64_t)j * kWideThreads);
+        in[j] = e < m;
+        at[j] = min(e, m - 2);
+        acc[j] = T(0.0);
     }
+    for (int32_t p = 0; p < P; ++p) {
+        const bool e = stale_select(ver_in[p], arrived[p], t, S);
+        const double *fp = fresh[p];
+        double *sp = slots[p];
+        const bool wr = e && fp != sp;
+        const double *src = e ? fp : sp;
+        T v[kWidePairs];
+#pragma unroll
+        for (int j = 0; j < kWidePairs; ++j)
+            v[j] = *(GlobalPtr<const T>)(src + at[j]);
+        if (wr) {
+#pragma unroll
+            for (int j = 0; j < kWidePairs; ++j)
+                if (in[j]) *(GlobalPtr<T>)(sp + at[j]) = v[j];
+        }
+#pragma unroll
+        for (int j = 0; j < kWidePairs; ++j) acc[j] = (p == 0) ? v[j] : acc[j] + v[j];
+    }
+#pragma unroll
+    for (int j = 0; j < kWidePairs; ++j)
+        if (in[j]) *(GlobalPtr<T>)(result + at[j]) = acc[j];
+}
+
+// The shape of the launch by the vectors' length.  Wide chunks (8 pairs per
+// thread, few ranks in flight) stream each rank's vector in long runs, and pay
+// once every CU has a workgroup (kReduceFill of them) and the ranks are many;
+// shorter vectors take chunks of one pair per thread with more ranks in
+// flight instead, and the shortest the split form.  Measured on MI355X, us per
+// call (a 1,024-thread workgroup of 16,384 elements, one rank in flight, for
+// every length before):
+//   256 x 4M      2,623 wide (1,024 x 8 pairs), 2,878 at 128 x 1 pair
+//   256 x 2M      1,329 at 512 x 8, 1,442 at 1,024 x 8, 1,532 at 128 x 1
+//   256 x 1M        659 at 256 x 8, 1,264 at 1,024 x 8, 778 at 128 x 1
+//   64 x 300,001     51 at 128 x 1, 125 at 256 x 8, 301 before; split 74
+//   2 x 8,000,001    41 at 256 x 2 pairs x 4 ranks, 45 at 128 x 1, 44 before
+//   24 x 30,011     4.5 split (the launch itself), 6.1 at 128 x 1, 74 before
+//   64 x 100,001     22 split, 20 at 128 x 1; 256 x 30,011: 22 and 38
+//   256 x 100        9 split at 64 x 1 element x 32 ranks, 12 at 128 x 1 pair
+constexpr int64_t kReduceFill = 200;        // workgroups that fill the 256 CUs well enough
+constexpr int32_t kReduceManyRanks = 16;    // wide chunks pay from here on
+constexpr int64_t kReduceSplitMax = 65536;  // elements: the split form up to here
+constexpr int64_t kReduceTinyMax = 4096;    // elements: single elements, 32 ranks in flight
+constexpr int32_t kReduceSplitRanks = 1024;
+
+template <int NTH, int W, int VP, int U, bool SPLIT>
+static ecc_status_t launch_reduce(ReduceArgs &a, hipStream_t stream) {
+    constexpr int64_t chunk = (int64_t)NTH * W * VP;
+    constexpr int64_t copy = (int64_t)NTH * W * kReduceCopies;
+    a.n_sum = (a.m + chunk - 1) / chunk;
+    const int64_t grid = 1 + a.n_sum + (SPLIT ? a.P * ((a.m + copy - 1) / copy) : 0);
+    if (grid > 0x7fffffff) {
+        set_error("m too large");
+        return ECC_ERR_RANGE;
+    }
+    hipLaunchKernelGGL((k_allreduce<NTH, W, VP, U, SPLIT>), dim3((unsigned)grid), dim3(NTH), 0,
+                       stream, a);
+    ECC_LAUNCH_CHECK();
+    return ECC_OK;
+}
+
+static ecc_status_t launch_reduce_any(ReduceArgs &a, hipStream_t stream) {
+    const int64_t m = a.m;
+    if (m <= kReduceSplitMax && a.P <= kReduceSplitRanks) {
+        if (m <= kReduceTinyMax) return launch_reduce<64, 1, 1, 32, true>(a, stream);
+        return launch_reduce<128, 2, 1, 16, true>(a, stream);
+    }
+    if (a.P >= kReduceManyRanks) {
+        constexpr int64_t wide = 2 * kWidePairs * kWideThreads;
+        const int64_t grid = 1 + (m + wide - 1) / wide;
+        if (grid > 0x7fffffff) {
+            set_error("m too large");
+            return ECC_ERR_RANGE;
+        }
+        if (m >= kReduceFill * wide) {
+            hipLaunchKernelGGL(k_allreduce_wide, dim3((unsigned)grid), dim3(kWideThreads), 0,
+                               stream, a.P, a.S, a.t, a.arrived, a.ver_in, a.ver_out, a.age_state,
+                               a.eff_state, a.forced, a.eff_user, a.result_clock, m, a.fresh,
+                               a.slots, a.result);
+            ECC_LAUNCH_CHECK();
+            return ECC_OK;
+        }
+        if (m >= kReduceFill * 8192) return launch_reduce<512, 2, 8, 1, false>(a, stream);
+        if (m >= kReduceFill * 4096) return launch_reduce<256, 2, 8, 2, false>(a, stream);
+    } else if (m >= (1 << 19)) {
+        return launch_reduce<256, 2, 2, 4, false>(a, stream);
+    }
+    if (m < 2) return launch_reduce<64, 1, 1, 8, false>(a, stream);
+    return launch_reduce<128, 2, 1, 8, false>(a, stream);
 }
 
 ecc_status_t launch_assemble(ecc_plan_t plan, const double *const *d_send,
@@ -266,20 +421,28 @@ ecc_status_t ecc_allreduce_partial(ecc_plan_t plan, int64_t m, const double *con
     ECC_ARG(d_fresh && d_slots, "d_fresh and d_slots must be device arrays of P pointers");
     ECC_ARG(d_arrived != nullptr, "d_arrived is NULL");
     ECC_ARG(d_result != nullptr || m == 0, "d_result is NULL");
-    const int64_t chunk = (int64_t)kReduceThreads * kReduceElems;
-    const int64_t grid = 1 + (m + chunk - 1) / chunk;
-    if (grid > 0x7fffffff) {
-        set_error("m too large");
-        return ECC_ERR_RANGE;
-    }
     const int64_t t = plan->clock;
-    const int32_t *ver_in = plan->d_version + (t & 1) * plan->P;
-    int32_t *ver_out = plan->d_version + ((t + 1) & 1) * plan->P;
-    TimedLaunch timed(plan, ECC_TIMING_ALLREDUCE);
-    hipLaunchKernelGGL(k_allreduce, dim3((unsigned)grid), dim3(kReduceThreads), 0, plan->stream,
-                       plan->P, plan->S, t, d_arrived, ver_in, ver_out, plan->d_age, plan->d_eff,
-                       plan->d_forced, d_eff_out, d_result_clock, m, d_fresh, d_slots, d_result);
-    ECC_LAUNCH_CHECK();
+    ReduceArgs a{};
+    a.P = plan->P;
+    a.S = plan->S;
+    a.t = t;
+    a.arrived = d_arrived;
+    a.ver_in = plan->d_version + (t & 1) * plan->P;
+    a.ver_out = plan->d_version + ((t + 1) & 1) * plan->P;
+    a.age_state = plan->d_age;
+    a.eff_state = plan->d_eff;
+    a.forced = plan->d_forced;
+    a.eff_user = d_eff_out;
+    a.result_clock = d_result_clock;
+    a.m = m;
+    a.fresh = d_fresh;
+    a.slots = d_slots;
+    a.result = d_result;
+    {
+        TimedLaunch timed(plan, ECC_TIMING_ALLREDUCE);
+        st = launch_reduce_any(a, plan->stream);
+    }
+    if (st != ECC_OK) return st;
     plan->clock = t + 1;
     return ECC_OK;
 }

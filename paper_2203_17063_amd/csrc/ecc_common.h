@@ -50,12 +50,6 @@ void clear_error();
 // ---------------------------------------------------------------------------
 constexpr int kAssembleThreads = 256;
 constexpr int kAssembleTile = 2048;      // elements copied by one workgroup
-// Partial allreduce block shape: 1,024 threads x 16 elements, so that a
-// workgroup streams 128 KB of each rank's vector at a time (measured on
-// MI355X: 5.45 TB/s at 256 ranks x 4M, against 4.89 TB/s with 256 x 4).
-constexpr int kReduceThreads = 1024;
-constexpr int kReduceElems = 16;  // elements per thread per rank (pairs of 16 B)
-constexpr int kReduceU = 1;       // ranks whose loads are in flight together
 constexpr int kSweepThreads = 256;
 constexpr int kStreamCap = 2048;         // nonzeros staged in LDS by a stream item
 constexpr int kStreamRows = 256;         // rows of one stream item at most
@@ -159,6 +153,29 @@ __device__ __forceinline__ bool stale_select(int32_t version, uint8_t arrived, i
     return version < 0 || arrived != 0 || (t - (int64_t)version) > (int64_t)S;
 }
 
+// W doubles moved by one access, at any 8-byte alignment (gfx950 takes 16-byte
+// accesses unaligned), and pointers into global memory whose address is not
+// a kernel argument (so that accesses need not be flat ones).
+template <int W>
+struct WordVec;
+template <>
+struct WordVec<1> {
+    typedef double t;
+};
+template <>
+struct WordVec<2> {
+    typedef double t __attribute__((ext_vector_type(2), aligned(8)));
+};
+template <typename T>
+using GlobalPtr = __attribute__((address_space(1))) T *;
+
+// A wave-uniform 64-bit value in scalar registers.
+__device__ __forceinline__ uint64_t wave_uniform(uint64_t x) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+    return (uint64_t)lo | ((uint64_t)hi << 32);
+}
+
 // 64-bit lane exchange through two 32-bit DPP moves.
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {
@@ -236,7 +253,7 @@ __device__ __forceinline__ double block_sum(double v, double *scratch) {
 // and ages, the eff flags, the forced-arrival count and the minimum version
 // (the clock of a reduced result).  Returns nothing; thread 0 writes.
 // record_step keeps one count per wave of the calling block: at most 16.
-static_assert(kAssembleThreads <= 1024 && kReduceThreads <= 1024 && kSweepThreads <= 1024,
+static_assert(kAssembleThreads <= 1024 && kSweepThreads <= 1024,
               "record_step holds 16 wave slots");
 __device__ __forceinline__ void record_step(int32_t P, int32_t S, int64_t t,
                                             const uint8_t *__restrict__ arrived,

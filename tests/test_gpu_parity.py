@@ -255,6 +255,61 @@ def test_allreduce_in_place(P, m, S, aligned):
     plan.close()
 
 
+@pytest.mark.parametrize("P,m", [
+    # (the split form up to 65,536 elements and 1,024 ranks, single elements
+    # up to 4,096; then chunks by length, wide ones from 16 ranks on)
+    (1, 2), (1, 4096), (2, 4097), (7, 65536), (5, 65537), (40, 65538), (300, 1), (300, 4099),
+    (1025, 1), (1025, 514), (3, (1 << 19) - 1), (3, (1 << 19) + 1), (16, 819199), (16, 819201),
+    (17, 200 * 8192 + 3), (16, 200 * 16384 + 1),
+])
+def test_allreduce_launch_shapes(P, m):
+    """Every launch shape of the partial allreduce, at the edges of its range:
+    results, slots and decisions bit for bit against sums in rank order, with
+    stale ranks, infinities, NaN and signed zeros, ranks already in place
+    (every fifth) and rows at both alignments (odd m)."""
+    E, R = _capi(), _runner()
+    announce("allreduce shapes", P, m)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(31 * P + m)
+    slots = torch.full((P, m), np.nan, dtype=torch.float64, device="cuda")
+    ref_slots = slots.clone()
+    result = torch.empty(m, dtype=torch.float64, device="cuda")
+    eff_d = torch.empty(P, dtype=torch.uint8, device="cuda")
+    d_slots = R.ptr_array(list(slots))
+    version = np.full(P, -1, dtype=np.int32)
+    plan = R.Plan(P, None, None, 1)
+    rng = np.random.default_rng(P + m)
+    for r in range(3):
+        fresh = torch.rand(P, m, generator=g, dtype=torch.float64, device="cuda") - 0.5
+        fresh[:, 0] = -0.0
+        if m > 2:
+            fresh[r % P, m - 1] = float("nan")
+            fresh[(r + 1) % P, m // 2] = float("inf")
+        mask = (rng.random(P) < 0.5).astype(np.uint8)
+        eff, _, _ = oracle.select(1, r, mask, version)
+        rows = []
+        for p in range(P):
+            in_place = p % 5 == 4
+            if in_place and eff[p]:
+                slots[p] = fresh[p]
+            rows.append(slots[p] if in_place else fresh[p])
+            if eff[p]:
+                ref_slots[p] = fresh[p]
+        d_fresh = R.ptr_array(rows)
+        E.ecc_allreduce_partial(plan.handle, m, d_fresh, d_slots, result,
+                                torch.from_numpy(mask).cuda(), eff_d)
+        ref = ref_slots[0].clone()
+        for p in range(1, P):
+            ref += ref_slots[p]
+        torch.cuda.synchronize()
+        assert np.array_equal(eff_d.cpu().numpy(), eff)
+        for got, want in ((result, ref), (slots, ref_slots)):
+            assert torch.equal(got.isnan(), want.isnan())
+            same = got.view(torch.int64) == want.view(torch.int64)
+            assert bool((same | want.isnan()).all()), (P, m, r)
+    plan.close()
+
+
 def test_partial_allreduce_full_sampled():
     """The benchmark's partial allreduce shape (256 ranks x 4M, 70% arrival, no staleness bound) for a
     few repetitions, checked at sampled indices against the last-arrival sum."""
