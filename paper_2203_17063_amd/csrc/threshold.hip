@@ -30,49 +30,60 @@ namespace ecc {
 constexpr int kThrThreads = 256;
 constexpr int kThrMaxStages = 5;  // Reduce: at most 32 processes in registers
 constexpr int kThrMaxStagesBig = 12;  // Reduce beyond 32 processes: up to 4096
-constexpr int kBcastTile = 4096;  // elements one workgroup copies
 
-// One workgroup per tile of kBcastTile elements of the prefix: the tile is
-// loaded from the root's vector once, into registers (kBcastPairs pairs per
-// thread), and stored into every other process's buffer -- 16-byte stores
-// where the destination row allows, else 8-byte.
-constexpr int kBcastPairs = kBcastTile / (2 * kThrThreads);
-
+// Broadcast: a workgroup loads a tile of the prefix (PAIRS pairs per thread)
+// from the root's vector into registers once and stores it into `per`
+// processes' buffers (blockIdx.y picks which).  Write-bound: 8 k P bytes.
+// The last pair of an odd prefix is moved back by one element (two lanes
+// then store the same value).
+template <int PAIRS>
 __global__ __launch_bounds__(kThrThreads) void k_bcast_prefix(int32_t P, int32_t root, int64_t k,
+                                                              int32_t per,
                                                               const double *__restrict__ src,
                                                               double *const *__restrict__ dst) {
-    const int64_t t0 = (int64_t)blockIdx.x * kBcastTile;
-    const bool src16 = ((uintptr_t)src & 15) == 0;
-    double2 v[kBcastPairs];
-#pragma unroll
-    for (int u = 0; u < kBcastPairs; ++u) {
-        const int64_t e = t0 + 2 * ((int64_t)threadIdx.x + (int64_t)u * kThrThreads);
-        if (e + 1 < k) {
-            if (src16) v[u] = *reinterpret_cast<const double2 *>(src + e);
-            else v[u] = make_double2(src[e], src[e + 1]);
-        } else {
-            v[u] = make_double2(e < k ? src[e] : 0.0, 0.0);
-        }
+    using T = typename WordVec<2>::t;
+    const int32_t p0 = (int32_t)blockIdx.y * per, p1 = min(P, p0 + per);
+    if (k == 1) {
+        if (threadIdx.x == 0)
+            for (int32_t p = p0; p < p1; ++p)
+                if (p != root) dst[p][0] = src[0];
+        return;
     }
-    for (int32_t p = 0; p < P; ++p) {
-        if (p == root) continue;
-        double *__restrict__ d = dst[p];
-        const bool d16 = ((uintptr_t)d & 15) == 0;
+    const int64_t t0 = (int64_t)blockIdx.x * (2 * PAIRS * kThrThreads);
+    T v[PAIRS];
+    int64_t at[PAIRS];
+    bool in[PAIRS];
 #pragma unroll
-        for (int u = 0; u < kBcastPairs; ++u) {
-            const int64_t e = t0 + 2 * ((int64_t)threadIdx.x + (int64_t)u * kThrThreads);
-            if (e + 1 < k) {
-                if (d16) *reinterpret_cast<double2 *>(d + e) = v[u];
-                else {
-                    d[e] = v[u].x;
-                    d[e + 1] = v[u].y;
-                }
-            } else if (e < k) {
-                d[e] = v[u].x;
-            }
+    for (int u = 0; u < PAIRS; ++u) {
+        const int64_t e = t0 + 2 * ((int64_t)threadIdx.x + (int64_t)u * kThrThreads);
+        in[u] = e < k;
+        at[u] = min(e, k - 2);
+        v[u] = *(GlobalPtr<const T>)(src + at[u]);
+    }
+    const bool whole = t0 + 2 * PAIRS * kThrThreads <= k;
+    for (int32_t p = p0; p < p1; ++p) {
+        if (p == root) continue;
+        double *d = dst[p];
+        if (whole) {
+#pragma unroll
+            for (int u = 0; u < PAIRS; ++u) *(GlobalPtr<T>)(d + at[u]) = v[u];
+        } else {
+#pragma unroll
+            for (int u = 0; u < PAIRS; ++u)
+                if (in[u]) *(GlobalPtr<T>)(d + at[u]) = v[u];
         }
     }
 }
+
+// Long prefixes take 4,096-element tiles written to every process; short ones
+// 512-element tiles, their processes split over enough workgroups (at least
+// kBcastRows processes each) to fill the device.  Measured on MI355X: 48 x
+// 22,509 elements 4.1 us, against 28 us in 4,096-element tiles (6
+// workgroups); 32 x 4.2M elements 172-194 us in those (5.5-6.2 TB/s; what
+// the kernel before it left to be written back counts here).
+constexpr int64_t kBcastLong = int64_t(1) << 21;  // elements: 512 workgroups of long tiles
+constexpr int32_t kBcastRows = 4;
+constexpr int64_t kBcastFill = 1024;
 
 // Reduce over relative ranks 0 .. n-1 (n <= 2^S) of the first k elements.
 // Every contribution is read once: non-temporal loads (measured on MI355X,
@@ -184,38 +195,85 @@ __global__ __launch_bounds__(kThrThreads) void k_reduce_bst_big(
     }
 }
 
-// Dropping partial allreduce: eight ranks' loads in flight, summed in rank
-// order; only arrived ranks are added.
-constexpr int kDropU = 8;
+// Dropping partial allreduce: result = +0.0 + the contributions of the ranks
+// that arrived, in rank order.  Read-bound: 8 m (arrived + 1) bytes.  Each
+// workgroup lists the arrived ranks' addresses in LDS (kDropStage ranks at a
+// time, in rank order), so that the loads of U ranks go out together without
+// a test or a pointer chase between them; each contribution is read once,
+// non-temporally, by one lane per element of a grid without a loop.
+// Measured on MI355X, 26 of 32 ranks x 8.4M: 332 us (5.5 TB/s), against 451
+// us for 2,048 resident workgroups walking the vector with eight ranks' loads
+// behind a test each; pairs per lane 337 to 371 us; 38 of 48 x 30,011: 5.0
+// against 12.7 us.
+constexpr int kDropStage = 256;
+
+constexpr int kDropU = 16;  // ranks whose loads are in flight together
 
 __global__ __launch_bounds__(kThrThreads) void k_allreduce_drop(int32_t P, int64_t m,
-                                                                const double *const *__restrict__ fresh,
-                                                                const uint8_t *__restrict__ arrived,
-                                                                double *__restrict__ result,
-                                                                int32_t *__restrict__ count) {
-    if (count && blockIdx.x == 0 && threadIdx.x == 0) {
-        int32_t c = 0;
-        for (int32_t p = 0; p < P; ++p) c += arrived[p] != 0;
-        *count = c;
-    }
-    const int64_t stride = (int64_t)gridDim.x * kThrThreads;
-    for (int64_t j = (int64_t)blockIdx.x * kThrThreads + threadIdx.x; j < m; j += stride) {
-        double acc = 0.0;
-        for (int32_t p0 = 0; p0 < P; p0 += kDropU) {
-            bool on[kDropU];
+                                                        const double *const *__restrict__ fresh,
+                                                        const uint8_t *__restrict__ arrived,
+                                                        double *__restrict__ result,
+                                                        int32_t *__restrict__ count) {
+    __shared__ uint64_t s_src[kDropStage];
+    __shared__ int32_t s_wave[kDropStage / 64];
+    const int tid = threadIdx.x;
+    const int64_t e = (int64_t)blockIdx.x * kThrThreads + tid;
+    const int64_t at = max<int64_t>(0, min(e, m - 1));
+    double acc = 0.0;
+    int32_t total = 0;
+    for (int32_t c0 = 0; c0 < P; c0 += kDropStage) {
+        if (c0) __syncthreads();
+        // the 64-rank groups of this stage, one wave at a time each
+        for (int32_t g = tid >> 6; g < kDropStage / 64; g += kThrThreads / 64) {
+            const int32_t p = c0 + g * 64 + (tid & 63);
+            const uint64_t on = __ballot(p < P && arrived[p] != 0);
+            if ((tid & 63) == 0) s_wave[g] = __popcll(on);
+        }
+        __syncthreads();
+        for (int32_t g = tid >> 6; g < kDropStage / 64; g += kThrThreads / 64) {
+            const int32_t p = c0 + g * 64 + (tid & 63);
+            const bool here = p < P && arrived[p] != 0;
+            const uint64_t on = __ballot(here);
+            int32_t at0 = 0;
+            for (int32_t h = 0; h < g; ++h) at0 += s_wave[h];
+            if (here && m > 0)
+                s_src[at0 + __popcll(on & ((1ull << (tid & 63)) - 1))] = (uint64_t)fresh[p];
+        }
+        int32_t nc = 0;
+#pragma unroll
+        for (int h = 0; h < kDropStage / 64; ++h) nc += s_wave[h];
+        total += nc;
+        __syncthreads();
+        if (m == 0) continue;
+        int32_t k = 0;
+        for (; k + kDropU <= nc; k += kDropU) {
+            uint64_t src[kDropU];
             double v[kDropU];
 #pragma unroll
-            for (int u = 0; u < kDropU; ++u) {
-                const int32_t p = p0 + u;
-                on[u] = p < P && arrived[p] != 0;
-                v[u] = on[u] ? fresh[p][j] : 0.0;
-            }
+            for (int u = 0; u < kDropU; ++u) src[u] = wave_uniform(s_src[k + u]);
 #pragma unroll
             for (int u = 0; u < kDropU; ++u)
-                if (on[u]) acc = acc + v[u];
+                v[u] = __builtin_nontemporal_load((GlobalPtr<const double>)((const double *)src[u] + at));
+#pragma unroll
+            for (int u = 0; u < kDropU; ++u) acc = acc + v[u];
         }
-        result[j] = acc;
+        if (k < nc) {
+            uint64_t src[kDropU];
+            double v[kDropU];
+#pragma unroll
+            for (int u = 0; u < kDropU; ++u) src[u] = wave_uniform(s_src[min(k + u, nc - 1)]);
+#pragma unroll
+            for (int u = 0; u < kDropU; ++u)
+                if (k + u < nc)
+                    v[u] = __builtin_nontemporal_load(
+                        (GlobalPtr<const double>)((const double *)src[u] + at));
+#pragma unroll
+            for (int u = 0; u < kDropU; ++u)
+                if (k + u < nc) acc = acc + v[u];
+        }
     }
+    if (e < m) result[e] = acc;
+    if (count && blockIdx.x == 0 && tid == 0) *count = total;
 }
 
 int64_t thr_prefix(double theta, int64_t m) {
@@ -228,15 +286,6 @@ int32_t thr_involved(double theta, int32_t P) {
     int64_t n = 1;
     while (n < need) n *= 2;
     return (int32_t)std::min<int64_t>(n, P);
-}
-
-int32_t thr_grid(int64_t elems) {
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        cus = 256;
-    const int64_t need = std::max<int64_t>(1, (elems + kThrThreads - 1) / kThrThreads);
-    return (int32_t)std::min<int64_t>(need, (int64_t)cus * 8);
 }
 
 int32_t thr_grid_once(int64_t elems) {
@@ -262,10 +311,22 @@ ecc_status_t ecc_bcast_threshold(int32_t P, int32_t root, int64_t m, double thet
     if (h_count) *h_count = k;
     if (k == 0 || P == 1) return ECC_OK;
     ECC_ARG(d_src != nullptr && d_dst != nullptr, "NULL source or destination array");
-    const int64_t tiles = (k + kBcastTile - 1) / kBcastTile;
+    const bool longer = k >= kBcastLong;
+    const int64_t tile = (longer ? 16 : 2) * kThrThreads;
+    const int64_t tiles = (k + tile - 1) / tile;
     ECC_ARG(tiles < 0x7fffffff, "too many tiles");
-    hipLaunchKernelGGL(k_bcast_prefix, dim3((unsigned)tiles), dim3(kThrThreads), 0,
-                       (hipStream_t)hip_stream, P, root, k, d_src, d_dst);
+    const int64_t groups = longer ? 1
+                                  : std::max<int64_t>(1, std::min<int64_t>(kBcastFill / tiles,
+                                                         (P + kBcastRows - 1) / kBcastRows));
+    const int32_t per = (int32_t)((P + groups - 1) / groups);
+    const dim3 grid((unsigned)tiles, (unsigned)((P + per - 1) / per));
+    hipStream_t st = (hipStream_t)hip_stream;
+    if (longer)
+        hipLaunchKernelGGL(k_bcast_prefix<8>, grid, dim3(kThrThreads), 0, st, P, root, k, per,
+                           d_src, d_dst);
+    else
+        hipLaunchKernelGGL(k_bcast_prefix<1>, grid, dim3(kThrThreads), 0, st, P, root, k, per,
+                           d_src, d_dst);
     ECC_LAUNCH_CHECK();
     return ECC_OK;
 }
@@ -326,7 +387,9 @@ ecc_status_t ecc_allreduce_drop(int32_t P, int64_t m, const double *const *d_fre
     ECC_ARG(d_arrived != nullptr, "d_arrived is NULL");
     ECC_ARG(m == 0 || (d_fresh && d_result), "NULL contribution array or result");
     if (m == 0 && !d_count) return ECC_OK;
-    hipLaunchKernelGGL(k_allreduce_drop, dim3(thr_grid(m)), dim3(kThrThreads), 0,
+    const int64_t grid = std::max<int64_t>(1, (m + kThrThreads - 1) / kThrThreads);
+    ECC_ARG(grid < 0x7fffffff, "m is too large");
+    hipLaunchKernelGGL(k_allreduce_drop, dim3((unsigned)grid), dim3(kThrThreads), 0,
                        (hipStream_t)hip_stream, P, m, d_fresh, d_arrived, d_result, d_count);
     ECC_LAUNCH_CHECK();
     return ECC_OK;

@@ -140,6 +140,43 @@ def test_allreduce_drop(P, q):
     assert int(cnt.item()) == int(arrived_h.sum())
 
 
+@pytest.mark.parametrize("P,m,root", [(2, 1, 0), (5, 2, 4), (9, 511, 3), (300, 513, 299),
+                                      (6, (1 << 21) - 1, 2), (3, 1 << 21, 0),
+                                      (4, (1 << 21) + 4097, 3)])
+def test_bcast_and_drop_shapes(P, m, root):
+    """Both tile sizes of the Broadcast at their edges, destinations at both
+    alignments (rows of m + 1), guards around every row; and the dropping
+    allreduce of the same rows (more ranks than one staged list, infinities,
+    NaN), bit for bit against sums in rank order."""
+    E = _E()
+    announce("bcast, drop shapes", P, m, root)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(P + m)
+    src = torch.rand(P, m, generator=g, dtype=torch.float64, device="cuda") - 0.5
+    src[:, 0] = -0.0
+    src[P - 1, m - 1] = float("inf")
+    if m > 2:
+        src[0, m // 2] = float("nan")
+    store = torch.full((P, m + 1), 7.0, dtype=torch.float64, device="cuda")
+    E.ecc_bcast_threshold(P, root, m, 1.0, src[root], _ptrs(list(store)), _stream())
+    want = torch.full_like(store, 7.0)
+    for p in range(P):
+        if p != root:
+            want[p, :m] = src[root]
+    assert torch.equal(store.view(torch.int64), want.view(torch.int64))
+    arrived = torch.from_numpy((np.random.default_rng(m).random(P) < 0.7).astype(np.uint8)).cuda()
+    res = torch.empty(m, dtype=torch.float64, device="cuda")
+    cnt = torch.zeros(1, dtype=torch.int32, device="cuda")
+    E.ecc_allreduce_drop(P, m, _ptrs(list(src)), arrived, res, cnt, _stream())
+    ref = torch.zeros(m, dtype=torch.float64, device="cuda")
+    for p in range(P):
+        if arrived[p]:
+            ref += src[p]
+    assert int(cnt) == int(arrived.sum())
+    same = res.view(torch.int64) == ref.view(torch.int64)
+    assert bool((same | (res.isnan() & ref.isnan())).all())
+
+
 @pytest.mark.parametrize("seed", range(4))
 def test_reduce_random(seed):
     """Random process counts (up to 64, or up to 4,096), roots, modes,
