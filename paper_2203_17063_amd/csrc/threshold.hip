@@ -208,8 +208,10 @@ __global__ __launch_bounds__(kThrThreads) void k_reduce_bst_big(
 constexpr int kDropStage = 256;
 
 constexpr int kDropU = 16;  // ranks whose loads are in flight together
+constexpr int64_t kDropLaunch = int64_t(1) << 31;  // elements of one launch
 
-__global__ __launch_bounds__(kThrThreads) void k_allreduce_drop(int32_t P, int64_t m,
+__global__ __launch_bounds__(kThrThreads) void k_allreduce_drop(int32_t P, int64_t e0,
+                                                        int64_t m,
                                                         const double *const *__restrict__ fresh,
                                                         const uint8_t *__restrict__ arrived,
                                                         double *__restrict__ result,
@@ -217,7 +219,7 @@ __global__ __launch_bounds__(kThrThreads) void k_allreduce_drop(int32_t P, int64
     __shared__ uint64_t s_src[kDropStage];
     __shared__ int32_t s_wave[kDropStage / 64];
     const int tid = threadIdx.x;
-    const int64_t e = (int64_t)blockIdx.x * kThrThreads + tid;
+    const int64_t e = e0 + (int64_t)blockIdx.x * kThrThreads + tid;
     const int64_t at = max<int64_t>(0, min(e, m - 1));
     double acc = 0.0;
     int32_t total = 0;
@@ -387,11 +389,17 @@ ecc_status_t ecc_allreduce_drop(int32_t P, int64_t m, const double *const *d_fre
     ECC_ARG(d_arrived != nullptr, "d_arrived is NULL");
     ECC_ARG(m == 0 || (d_fresh && d_result), "NULL contribution array or result");
     if (m == 0 && !d_count) return ECC_OK;
-    const int64_t grid = std::max<int64_t>(1, (m + kThrThreads - 1) / kThrThreads);
-    ECC_ARG(grid < 0x7fffffff, "m is too large");
-    hipLaunchKernelGGL(k_allreduce_drop, dim3((unsigned)grid), dim3(kThrThreads), 0,
-                       (hipStream_t)hip_stream, P, m, d_fresh, d_arrived, d_result, d_count);
-    ECC_LAUNCH_CHECK();
+    // (a launch holds fewer than 2^32 threads)
+    int64_t e0 = 0;
+    do {
+        const int64_t grid = std::max<int64_t>(
+            1, (std::min(m - e0, kDropLaunch) + kThrThreads - 1) / kThrThreads);
+        hipLaunchKernelGGL(k_allreduce_drop, dim3((unsigned)grid), dim3(kThrThreads), 0,
+                           (hipStream_t)hip_stream, P, e0, m, d_fresh, d_arrived, d_result,
+                           e0 == 0 ? d_count : nullptr);
+        ECC_LAUNCH_CHECK();
+        e0 += kDropLaunch;
+    } while (e0 < m);
     return ECC_OK;
 }
 

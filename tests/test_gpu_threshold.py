@@ -202,6 +202,25 @@ def test_reduce_random(seed):
     assert np.array_equal(res.cpu().numpy(), res_h)
 
 
+def test_allreduce_drop_beyond_one_launch():
+    """A vector of more elements than one launch has threads (2^32): every
+    element is summed, two launches' worth past the first boundary."""
+    E = _E()
+    m = (1 << 32) + 515
+    announce("drop, 2^32 elements", m)
+    x = torch.empty(m, dtype=torch.float64, device="cuda")
+    x.uniform_(-1.0, 1.0)
+    res = torch.zeros(m, dtype=torch.float64, device="cuda")
+    arrived = torch.ones(1, dtype=torch.uint8, device="cuda")
+    cnt = torch.zeros(1, dtype=torch.int32, device="cuda")
+    E.ecc_allreduce_drop(1, m, _ptrs([x]), arrived, res, cnt, _stream())
+    torch.cuda.synchronize()
+    assert int(cnt.item()) == 1
+    step = 1 << 30
+    for a in range(0, m, step):
+        assert bool((res[a:a + step] == x[a:a + step]).all()), a
+
+
 def test_threshold_errors():
     E = _E()
     announce("threshold errors")
