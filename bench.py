@@ -52,8 +52,10 @@ def format_sweep_bytes(n, nnz, form, row_class):
     """The same for the bytes the library's copy of the matrix holds: the
     diagonal form reads values by diagonal (row_class per row, absent ones
     included) and a mask byte per row, and no column indices or row
-    pointers; the column-value form one value per column in place of one
+    pointers; with constant diagonals the mask byte alone; the column-value form one value per column in place of one
     per nonzero.  The general form: the CSR model."""
+    if form == "constant diagonals":
+        return n + 24 * n
     if form == "diagonals":
         return 8 * row_class * n + n + 24 * n
     if form == "column values":
@@ -229,6 +231,8 @@ def run_iterative_gpu(cfg, prob, steps, warmup):
     form_id, offsets = E.ecc_matrix_form(run.mat)
     form = {E.ECC_FORM_GENERAL: "general", E.ECC_FORM_COLUMN_VALUES: "column values",
             E.ECC_FORM_DIAGONALS: "diagonals"}[form_id]
+    if E.ecc_matrix_diagonal_values(run.mat) is not None:
+        form = "constant diagonals"
     probe = None
     if layout in (E.ECC_LAYOUT_SORTED, E.ECC_LAYOUT_RANGES):
         probe = gather_probe(prob, run, slots if layout == E.ECC_LAYOUT_RANGES else 1)

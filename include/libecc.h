@@ -260,7 +260,11 @@ ecc_status_t ecc_allreduce_partial(ecc_plan_t plan, int64_t m, const double *con
  * keeps each row's values by diagonal and one byte per row naming the
  * diagonals it holds, in place of the column indices (8 bytes x R per row
  * instead of 12 bytes x R); diagonals are summed in increasing offset order,
- * which is the rows' CSR order.
+ * which is the rows' CSR order.  Where moreover all entries of each diagonal
+ * hold one value, bit for bit (a stencil of constant coefficients), and the
+ * problem is not one for ECC_SCHEDULE_SINGLE, the copy keeps that value per
+ * diagonal in place of the rows' values: the byte per row is all it holds
+ * (see ecc_matrix_diagonal_values).
  * Column values (ECC_KIND_POWER in ECC_LAYOUT_SORTED or ECC_LAYOUT_RANGES):
  * when all entries of every column j hold one value c_j, bit for bit -- the
  * PageRank matrix W = A^T D^-1 of Section IV holds 1 / outdeg(j) throughout
@@ -346,6 +350,12 @@ ecc_status_t ecc_matrix_tiling(ecc_matrix_t A, int64_t *plane_rows, int64_t *til
 #define ECC_MAX_DIAGONALS 8
 ecc_status_t ecc_matrix_form(ecc_matrix_t A, int32_t *form, int32_t *n_diagonals,
                              int32_t *offsets);
+
+/* Constant diagonals: *constant = 1 when the diagonal form keeps one value
+ * per diagonal instead of values by row, whose n_diagonals values go to
+ * values (ECC_MAX_DIAGONALS doubles or NULL; 0 beyond, and 0 throughout when
+ * *constant = 0).  Host only.  ECC_ERR_ARG for a NULL matrix or constant. */
+ecc_status_t ecc_matrix_diagonal_values(ecc_matrix_t A, int32_t *constant, double *values);
 
 /* Schedule chosen at set-up (host only): ECC_SCHEDULE_STATIC,
  * ECC_SCHEDULE_QUEUE or ECC_SCHEDULE_SINGLE. */

@@ -79,6 +79,7 @@ _SIGS = [
     ("ecc_matrix_tiling", ctypes.c_int, [_VP, _VP, _VP]),
     ("ecc_matrix_schedule", ctypes.c_int, [_VP, _VP]),
     ("ecc_matrix_form", ctypes.c_int, [_VP, _VP, _VP, _VP]),
+    ("ecc_matrix_diagonal_values", ctypes.c_int, [_VP, _VP, _VP]),
     ("ecc_partials_size", _I64, [_VP]),
     ("ecc_matrix_layout", ctypes.c_int, [_VP, _VP, _VP]),
     ("ecc_iterate_jacobi", ctypes.c_int, [_VP, _VP, _VP, _VP, _VP, _VP, _VP]),
@@ -265,6 +266,15 @@ def ecc_matrix_form(mat):
     offs = (ctypes.c_int32 * ECC_MAX_DIAGONALS)()
     _check(lib().ecc_matrix_form(mat, ctypes.byref(form), ctypes.byref(nd), offs))
     return form.value, list(offs[:nd.value])
+
+
+def ecc_matrix_diagonal_values(mat):
+    """The value of each diagonal where the diagonal form keeps one value per
+    diagonal, else None."""
+    const = ctypes.c_int32(0)
+    vals = (ctypes.c_double * ECC_MAX_DIAGONALS)()
+    _check(lib().ecc_matrix_diagonal_values(mat, ctypes.byref(const), vals))
+    return list(vals[:len(ecc_matrix_form(mat)[1])]) if const.value else None
 
 
 def ecc_matrix_destroy(mat):

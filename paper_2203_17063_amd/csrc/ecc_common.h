@@ -64,6 +64,9 @@ constexpr int kDiagMax = ECC_MAX_DIAGONALS;
 struct DiagOffsets {
     int32_t v[kDiagMax];
 };
+struct DiagValues {
+    double v[kDiagMax];
+};
 
 // One assembly tile: `len` elements of rank `rank` starting `off` elements
 // into its block.
@@ -429,6 +432,8 @@ struct ecc_matrix_s {
     bool dia = false;               // short layout in diagonal form (d_ell_mask, no d_ell_col)
     int32_t n_dia = 0;              // its diagonals
     ecc::DiagOffsets dia_off{};     // their offsets, ascending
+    bool dia_const = false;         // every diagonal holds one value (no d_ell_val)
+    ecc::DiagValues dia_val{};      // those values
     double *d_ell_val = nullptr;    // short layout: their values
     int64_t tile_plane = 0;         // short layout: plane rows of the tiled item order (0: row order)
     int64_t tile_rows = 0;          // short layout: rows per tile

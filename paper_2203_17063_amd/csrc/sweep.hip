@@ -49,6 +49,7 @@
 // rank arrives.  No entry of x_hat that is written is read in the same
 // launch, so the fused step equals assemble-then-sweep bit for bit.
 #include <algorithm>
+#include <cstring>
 #include <mutex>
 #include <vector>
 
@@ -91,6 +92,7 @@ struct SweepArgs {
     const double *ell_val;
     const uint8_t *ell_mask;  // short layout, diagonal form: the diagonals of each row
     DiagOffsets dia;          // and their offsets
+    DiagValues dia_val;       // constant diagonals: the value of each
     int64_t ell_n;
     int32_t interleave;  // items dealt round-robin instead of in XCD ranges
     int32_t reserve0;    // workgroup 0 takes no items (grids of kReserveMinGrid or more)
@@ -785,31 +787,73 @@ __global__ __launch_bounds__(kFinishThreads) void k_range_finish(RangeFinishArgs
 // consecutive words and an item's entries are one contiguous run of the
 // copy, which is laid out in the order the items are swept.  Padding past a
 // row's end has column -1.
-// In the diagonal form (DIA) plane k holds the row's entry on diagonal k
-// (column row + dia.v[k]), and a byte per row (at [base + l]) says which
-// diagonals the row holds: no column indices are stored.  Diagonals are in
-// ascending order of offset, so for rows whose entries are sorted by column
-// plane order is CSR order.
-template <int R>
+// In the diagonal forms plane k holds the row's entry on diagonal k (column
+// row + dia.v[k]), and a byte per row (at [base + l]) says which diagonals
+// the row holds: no column indices are stored, and a lane keeps the byte in
+// place of the columns.  Diagonals are in ascending order of offset, so for
+// rows whose entries are sorted by column plane order is CSR order.
+// With constant diagonals (every entry of diagonal k holds one value,
+// dia_val.v[k]) no planes are stored either: a sweep reads one byte per row
+// of the matrix, 1 in place of 8 R + 1.  The products are those of the
+// stored values, bit for bit.  Measured on MI355X (Jacobi on the 400^3
+// 7-point stencil, 512 ranks): 845 us per iteration against 1,246 with the
+// value planes.
+enum { kFormGeneral = 0, kFormDia = 1, kFormDiaConst = 2 };
+
+template <int R, int FORM>
 struct EllEntries {
     int32_t c[R];
     double v[R];
+    __device__ __forceinline__ bool held(int j) const { return c[j] >= 0; }
+    __device__ __forceinline__ int32_t col(int j, int32_t, const SweepArgs &) const { return c[j]; }
+    __device__ __forceinline__ bool diag(int j, int32_t i, const SweepArgs &) const {
+        return c[j] == i;
+    }
+    __device__ __forceinline__ double val(int j, const SweepArgs &) const { return v[j]; }
 };
 
+template <int R>
+struct EllEntries<R, kFormDia> {
+    uint32_t mk;
+    double v[R];
+    __device__ __forceinline__ bool held(int j) const { return (mk >> j) & 1u; }
+    __device__ __forceinline__ int32_t col(int j, int32_t i, const SweepArgs &a) const {
+        return i + a.dia.v[j];
+    }
+    __device__ __forceinline__ bool diag(int j, int32_t, const SweepArgs &a) const {
+        return a.dia.v[j] == 0;
+    }
+    __device__ __forceinline__ double val(int j, const SweepArgs &) const { return v[j]; }
+};
 
-template <int R, bool DIA>
+template <int R>
+struct EllEntries<R, kFormDiaConst> {
+    uint32_t mk;
+    __device__ __forceinline__ bool held(int j) const { return (mk >> j) & 1u; }
+    __device__ __forceinline__ int32_t col(int j, int32_t i, const SweepArgs &a) const {
+        return i + a.dia.v[j];
+    }
+    __device__ __forceinline__ bool diag(int j, int32_t, const SweepArgs &a) const {
+        return a.dia.v[j] == 0;
+    }
+    __device__ __forceinline__ double val(int j, const SweepArgs &a) const {
+        return a.dia_val.v[j];
+    }
+};
+
+template <int R, int FORM>
 __device__ __forceinline__ void ell_entries(const SweepArgs &a, bool live, const WorkItem &w,
-                                            int32_t l, EllEntries<R> &e) {
-    const int64_t base = (int64_t)w.k0 * R + l;
-    const int32_t pad = sell_pad(w.nrows);
-    uint32_t mk = 0;
-    if constexpr (DIA) mk = live ? a.ell_mask[(int64_t)w.k0 + l] : 0u;
+                                            int32_t l, EllEntries<R, FORM> &e) {
+    if constexpr (FORM != kFormGeneral) e.mk = live ? a.ell_mask[(int64_t)w.k0 + l] : 0u;
+    if constexpr (FORM != kFormDiaConst) {
+        const int64_t base = (int64_t)w.k0 * R + l;
+        const int32_t pad = sell_pad(w.nrows);
 #pragma unroll
-    for (int j = 0; j < R; ++j) {
-        const int64_t k = base + (int64_t)j * pad;
-        if constexpr (DIA) e.c[j] = ((mk >> j) & 1u) ? w.row0 + l + a.dia.v[j] : -1;
-        else e.c[j] = live ? a.ell_col[k] : -1;
-        e.v[j] = live ? a.ell_val[k] : 0.0;
+        for (int j = 0; j < R; ++j) {
+            const int64_t k = base + (int64_t)j * pad;
+            if constexpr (FORM == kFormGeneral) e.c[j] = live ? a.ell_col[k] : -1;
+            e.v[j] = live ? a.ell_val[k] : 0.0;
+        }
     }
 }
 
@@ -817,7 +861,7 @@ __device__ __forceinline__ void ell_entries(const SweepArgs &a, bool live, const
 // two-deep pipeline over the workgroup's items: a row's entries depend only
 // on the item's descriptor, so while the gathers of item n are in flight
 // the entries of item n + 1 are loaded (and the descriptor of item n + 2).
-template <int KIND, bool STEP, int R, bool DIA>
+template <int KIND, bool STEP, int R, int FORM>
 __device__ __forceinline__ void short_body(const SweepArgs &a) {
     __shared__ double s_red[kSweepThreads / 64];
     __shared__ uint8_t s_eff[STEP ? kFusedMaxP : 1];
@@ -830,9 +874,9 @@ __device__ __forceinline__ void short_body(const SweepArgs &a) {
     bool have = w < i_end;
     bool have_next = have && (int64_t)w + w_step < i_end;
     WorkItem cur{}, nxt{};
-    EllEntries<R> E;
+    EllEntries<R, FORM> E;
     if (have) cur = a.items[w];
-    ell_entries<R, DIA>(a, have && tid < cur.nrows, cur, tid, E);
+    ell_entries<R, FORM>(a, have && tid < cur.nrows, cur, tid, E);
     if (have_next) nxt = a.items[w + w_step];
     StepView sv{s_eff, s_bs, a.P};
     sweep_prologue<STEP>(a, s_eff, s_bs, s_red);
@@ -850,23 +894,23 @@ __device__ __forceinline__ void short_body(const SweepArgs &a) {
 #pragma unroll
         for (int j = 0; j < R; ++j)
             // Jacobi sums the diagonal entry apart: no gather for it
-            y[j] = (E.c[j] >= 0 && !(KIND == ECC_KIND_JACOBI && E.c[j] == i))
-                       ? view_load<STEP>(E.c[j], cur.lo, cur.hi, a.x_own, a.x_hat, sv, rc)
+            y[j] = (E.held(j) && !(KIND == ECC_KIND_JACOBI && E.diag(j, i, a)))
+                       ? view_load<STEP>(E.col(j, i, a), cur.lo, cur.hi, a.x_own, a.x_hat, sv, rc)
                        : 0.0;
         double xo = 0.0, bi = 0.0;
         if (live) {
             xo = a.x_own[i];
             if (KIND == ECC_KIND_JACOBI) bi = a.b[i];
         }
-        EllEntries<R> En;
-        ell_entries<R, DIA>(a, have_next && tid < nxt.nrows, nxt, tid, En);
+        EllEntries<R, FORM> En;
+        ell_entries<R, FORM>(a, have_next && tid < nxt.nrows, nxt, tid, En);
         if (live) {
             double s = 0.0, dg = 0.0;
 #pragma unroll
             for (int j = 0; j < R; ++j) {
-                if (E.c[j] >= 0) {
-                    if (KIND == ECC_KIND_JACOBI && E.c[j] == i) dg = E.v[j];
-                    else s = s + E.v[j] * y[j];
+                if (E.held(j)) {
+                    if (KIND == ECC_KIND_JACOBI && E.diag(j, i, a)) dg = E.val(j, a);
+                    else s = s + E.val(j, a) * y[j];
                 }
             }
             if (STEP && s_eff[cur.rank] != 0) a.x_hat[i] = xo;
@@ -922,7 +966,7 @@ __device__ __forceinline__ int xcc_id() {
 // short_body: tickets are taken three items ahead by thread 0 and handed to
 // the workgroup through LDS at the one barrier per item, where the item's
 // partial norm is also assembled.
-template <int KIND, bool STEP, int R, bool DIA>
+template <int KIND, bool STEP, int R, int FORM>
 __device__ __forceinline__ void short_body_queue(const SweepArgs &a) {
     __shared__ double s_red[kSweepThreads / 64];
     __shared__ double s_ws[2][kSweepThreads / 64];
@@ -941,9 +985,9 @@ __device__ __forceinline__ void short_body_queue(const SweepArgs &a) {
     __syncthreads();
     int32_t w = s_tk[2], wn = s_tk[3], wnn = s_tk[4];
     WorkItem cur{}, nxt{};
-    EllEntries<R> E;
+    EllEntries<R, FORM> E;
     if (w >= 0) cur = a.items[w];
-    ell_entries<R, DIA>(a, w >= 0 && tid < cur.nrows, cur, tid, E);
+    ell_entries<R, FORM>(a, w >= 0 && tid < cur.nrows, cur, tid, E);
     if (wn >= 0) nxt = a.items[wn];
     RankCache rc;
     int kk = 0;
@@ -958,24 +1002,24 @@ __device__ __forceinline__ void short_body_queue(const SweepArgs &a) {
 #pragma unroll
         for (int j = 0; j < R; ++j)
             // Jacobi sums the diagonal entry apart: no gather for it
-            y[j] = (E.c[j] >= 0 && !(KIND == ECC_KIND_JACOBI && E.c[j] == i))
-                       ? view_load<STEP>(E.c[j], cur.lo, cur.hi, a.x_own, a.x_hat, sv, rc)
+            y[j] = (E.held(j) && !(KIND == ECC_KIND_JACOBI && E.diag(j, i, a)))
+                       ? view_load<STEP>(E.col(j, i, a), cur.lo, cur.hi, a.x_own, a.x_hat, sv, rc)
                        : 0.0;
         double xo = 0.0, bi = 0.0;
         if (live) {
             xo = a.x_own[i];
             if (KIND == ECC_KIND_JACOBI) bi = a.b[i];
         }
-        EllEntries<R> En;
-        ell_entries<R, DIA>(a, wn >= 0 && tid < nxt.nrows, nxt, tid, En);
+        EllEntries<R, FORM> En;
+        ell_entries<R, FORM>(a, wn >= 0 && tid < nxt.nrows, nxt, tid, En);
         double c = 0.0;
         if (live) {
             double s = 0.0, dg = 0.0;
 #pragma unroll
             for (int j = 0; j < R; ++j) {
-                if (E.c[j] >= 0) {
-                    if (KIND == ECC_KIND_JACOBI && E.c[j] == i) dg = E.v[j];
-                    else s = s + E.v[j] * y[j];
+                if (E.held(j)) {
+                    if (KIND == ECC_KIND_JACOBI && E.diag(j, i, a)) dg = E.val(j, a);
+                    else s = s + E.val(j, a) * y[j];
                 }
             }
             if (STEP && s_eff[cur.rank] != 0) a.x_hat[i] = xo;
@@ -1041,15 +1085,16 @@ __global__ void k_build_ell(int64_t n_items, int32_t R, const WorkItem *__restri
 // without spilling -- 8 for rows of up to 4 entries, 7 for 5, 5 for 7 or 8
 // (the fused Jacobi kernel: 61, 69 and 85-93 VGPRs; 8 waves at R = 5 would
 // spill).
-template <int R>
+template <int R, int FORM>
 constexpr int short_waves() {
-    return R <= 4 ? 8 : (R == 5 ? 7 : 5);
+    return R <= 4 || FORM == kFormDiaConst ? 8 : (R == 5 ? 7 : 5);
 }
-template <int KIND, bool STEP, int R, bool QUEUE, bool DIA>
-__global__ __launch_bounds__(kSweepThreads) __attribute__((amdgpu_waves_per_eu(short_waves<R>())))
+template <int KIND, bool STEP, int R, bool QUEUE, int FORM>
+__global__ __launch_bounds__(kSweepThreads)
+__attribute__((amdgpu_waves_per_eu(short_waves<R, FORM>())))
 void k_sweep_short(SweepArgs a) {
-    if constexpr (QUEUE) short_body_queue<KIND, STEP, R, DIA>(a);
-    else short_body<KIND, STEP, R, DIA>(a);
+    if constexpr (QUEUE) short_body_queue<KIND, STEP, R, FORM>(a);
+    else short_body<KIND, STEP, R, FORM>(a);
 }
 
 // Diagonal form: the distinct offsets col - row of a short-row matrix's
@@ -1102,10 +1147,64 @@ __global__ void k_diag_set(int32_t n_rows, const int32_t *__restrict__ row_ptr,
     }
 }
 
+// Constant diagonals: one value, bit for bit, for each of the D diagonals a
+// workgroup's rows hold (kDiagMax per workgroup in `rep`; the ones it holds
+// in have[]), or bad raised.  Rows already checked to lie on `off`.  A thread
+// stops at its first differing entry, so a matrix of varying coefficients
+// costs a few rows per thread.
+__global__ void k_diag_values(int32_t n_rows, int32_t D, DiagOffsets off,
+                              const int32_t *__restrict__ row_ptr,
+                              const int32_t *__restrict__ col, const double *__restrict__ val,
+                              unsigned long long *__restrict__ rep, uint32_t *__restrict__ have,
+                              uint32_t *__restrict__ bad) {
+    __shared__ unsigned long long s_rep[kDiagMax];
+    __shared__ uint32_t s_have, s_bad;
+    if (threadIdx.x == 0) s_have = s_bad = 0;
+    __syncthreads();
+    unsigned long long mine[kDiagMax];
+    uint32_t seen = 0;
+    bool differs = false;
+#pragma unroll
+    for (int j = 0; j < kDiagMax; ++j) mine[j] = 0;
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n_rows && !differs;
+         i += gridDim.x * blockDim.x) {
+        for (int32_t k = row_ptr[i]; k < row_ptr[i + 1]; ++k) {
+            const int32_t d = col[k] - i;
+            const unsigned long long v = (unsigned long long)__double_as_longlong(val[k]);
+#pragma unroll
+            for (int j = 0; j < kDiagMax; ++j) {
+                if (j < D && off.v[j] == d) {
+                    if (!((seen >> j) & 1u)) mine[j] = v;
+                    else if (mine[j] != v) differs = true;
+                    seen |= 1u << j;
+                }
+            }
+        }
+    }
+    // one thread's value per diagonal stands for the workgroup
+#pragma unroll
+    for (int j = 0; j < kDiagMax; ++j)
+        if (((seen >> j) & 1u) && !((atomicOr(&s_have, 1u << j) >> j) & 1u)) s_rep[j] = mine[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kDiagMax; ++j)
+        if (((seen >> j) & 1u) && s_rep[j] != mine[j]) differs = true;
+    if (differs) s_bad = 1;
+    __syncthreads();
+    if (threadIdx.x < kDiagMax)
+        rep[(int64_t)blockIdx.x * kDiagMax + threadIdx.x] =
+            ((s_have >> threadIdx.x) & 1u) ? s_rep[threadIdx.x] : 0;
+    if (threadIdx.x == 0) {
+        have[blockIdx.x] = s_have;
+        if (s_bad) *bad = 1;
+    }
+}
+
 // The diagonal form of the item-major copy (layout as in ell_entries), one
 // workgroup per item: lane l writes its row's value planes (0 where the row
 // holds no entry on a diagonal) and its diagonal mask.  Columns of rows
-// already checked to lie on the D offsets in `off`.
+// already checked to lie on the D offsets in `off`.  Constant diagonals:
+// ell_val is null, only the masks are written.
 __global__ void k_build_dia(int64_t n_items, int32_t R, int32_t D, DiagOffsets off,
                             const WorkItem *__restrict__ items,
                             const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
@@ -1117,7 +1216,8 @@ __global__ void k_build_dia(int64_t n_items, int32_t R, int32_t D, DiagOffsets o
         const int32_t l = threadIdx.x;
         if (l >= pad) continue;
         const int64_t base = (int64_t)it.k0 * R + l;
-        for (int32_t j = 0; j < R; ++j) ell_val[base + (int64_t)j * pad] = 0.0;
+        if (ell_val)
+            for (int32_t j = 0; j < R; ++j) ell_val[base + (int64_t)j * pad] = 0.0;
         uint32_t mk = 0;
         if (l < it.nrows) {
             const int32_t i = it.row0 + l;
@@ -1125,7 +1225,7 @@ __global__ void k_build_dia(int64_t n_items, int32_t R, int32_t D, DiagOffsets o
                 const int32_t d = col[k] - i;
                 int32_t j = 0;
                 while (j < D - 1 && off.v[j] != d) ++j;
-                ell_val[base + (int64_t)j * pad] = val[k];
+                if (ell_val) ell_val[base + (int64_t)j * pad] = val[k];
                 mk |= 1u << j;
             }
         }
@@ -1676,13 +1776,13 @@ static hipError_t sweep_occupancy(int *per_cu, int kind, bool colscale) {
                      per_cu, k_sweep<ECC_KIND_POWER, S, LAY>, kSweepThreads, 0);
 }
 
-template <int R, bool DIA>
+template <int R, int FORM>
 static hipError_t short_occupancy_r(int *per_cu, int kind) {
     return kind == ECC_KIND_JACOBI
                ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                     per_cu, k_sweep_short<ECC_KIND_JACOBI, true, R, false, DIA>, kSweepThreads, 0)
+                     per_cu, k_sweep_short<ECC_KIND_JACOBI, true, R, false, FORM>, kSweepThreads, 0)
                : hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                     per_cu, k_sweep_short<ECC_KIND_POWER, true, R, false, DIA>, kSweepThreads, 0);
+                     per_cu, k_sweep_short<ECC_KIND_POWER, true, R, false, FORM>, kSweepThreads, 0);
 }
 
 // Entries per row of the short-layout kernel that serves rows of at most
@@ -1691,19 +1791,38 @@ static int short_class(int32_t max_row) {
     return max_row <= 3 ? 3 : max_row == 4 ? 4 : max_row == 5 ? 5 : max_row <= 7 ? 7 : 8;
 }
 
-template <bool DIA>
+template <int FORM>
 static hipError_t short_occupancy(int *per_cu, int kind, int32_t short_r) {
     switch (short_class(short_r)) {
-        case 3: return short_occupancy_r<3, DIA>(per_cu, kind);
-        case 4: return short_occupancy_r<4, DIA>(per_cu, kind);
-        case 5: return short_occupancy_r<5, DIA>(per_cu, kind);
-        case 7: return short_occupancy_r<7, DIA>(per_cu, kind);
-        default: return short_occupancy_r<8, DIA>(per_cu, kind);
+        case 3: return short_occupancy_r<3, FORM>(per_cu, kind);
+        case 4: return short_occupancy_r<4, FORM>(per_cu, kind);
+        case 5: return short_occupancy_r<5, FORM>(per_cu, kind);
+        case 7: return short_occupancy_r<7, FORM>(per_cu, kind);
+        default: return short_occupancy_r<8, FORM>(per_cu, kind);
     }
 }
 
+// The workgroups' values of each diagonal (k_diag_values) as one, or false
+// where two of them differ.
+static bool merge_diag_values(int blocks, const unsigned long long *rep, const uint32_t *have,
+                              DiagValues &out) {
+    unsigned long long one[kDiagMax] = {};
+    uint32_t got = 0;
+    for (int b = 0; b < blocks; ++b)
+        for (int j = 0; j < kDiagMax; ++j) {
+            if (!((have[b] >> j) & 1u)) continue;
+            const unsigned long long v = rep[(size_t)b * kDiagMax + j];
+            if (((got >> j) & 1u) && one[j] != v) return false;
+            one[j] = v;
+            got |= 1u << j;
+        }
+    static_assert(sizeof(one) == sizeof(out.v), "one 64-bit value per diagonal");
+    std::memcpy(out.v, one, sizeof(one));
+    return true;
+}
+
 static int32_t sweep_grid(int64_t n_items, int kind, int layout, int32_t short_r,
-                          bool colscale, bool dia) {
+                          bool colscale, int form) {
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
@@ -1711,8 +1830,10 @@ static int32_t sweep_grid(int64_t n_items, int kind, int layout, int32_t short_r
     const hipError_t e =
         layout == kLaySorted   ? sweep_occupancy<kLaySorted>(&per_cu, kind, colscale)
         : layout == kLayRanges ? sweep_occupancy<kLayRanges>(&per_cu, kind, colscale)
-        : layout == kLayShort  ? (dia ? short_occupancy<true>(&per_cu, kind, short_r)
-                                      : short_occupancy<false>(&per_cu, kind, short_r))
+        : layout == kLayShort  ? (form == kFormDiaConst ? short_occupancy<kFormDiaConst>(&per_cu, kind, short_r)
+                                  : form == kFormDia
+                                      ? short_occupancy<kFormDia>(&per_cu, kind, short_r)
+                                      : short_occupancy<kFormGeneral>(&per_cu, kind, short_r))
                                : sweep_occupancy<kLayStream>(&per_cu, kind, false);
     if (e != hipSuccess || per_cu < 1) per_cu = 4;
     const int64_t resident = (int64_t)std::max(cus, 1) * per_cu;
@@ -1722,15 +1843,15 @@ static int32_t sweep_grid(int64_t n_items, int kind, int layout, int32_t short_r
 }
 
 // The short-row kernel of a matrix's row class.
-template <int K, bool S, bool Q, bool D>
+template <int K, bool S, bool Q, int F>
 static void launch_short(ecc_matrix_t M, dim3 grid, dim3 block, hipStream_t st,
                          const SweepArgs &a) {
     switch (short_class(M->short_r)) {
-        case 3: hipLaunchKernelGGL((k_sweep_short<K, S, 3, Q, D>), grid, block, 0, st, a); break;
-        case 4: hipLaunchKernelGGL((k_sweep_short<K, S, 4, Q, D>), grid, block, 0, st, a); break;
-        case 5: hipLaunchKernelGGL((k_sweep_short<K, S, 5, Q, D>), grid, block, 0, st, a); break;
-        case 7: hipLaunchKernelGGL((k_sweep_short<K, S, 7, Q, D>), grid, block, 0, st, a); break;
-        default: hipLaunchKernelGGL((k_sweep_short<K, S, 8, Q, D>), grid, block, 0, st, a); break;
+        case 3: hipLaunchKernelGGL((k_sweep_short<K, S, 3, Q, F>), grid, block, 0, st, a); break;
+        case 4: hipLaunchKernelGGL((k_sweep_short<K, S, 4, Q, F>), grid, block, 0, st, a); break;
+        case 5: hipLaunchKernelGGL((k_sweep_short<K, S, 5, Q, F>), grid, block, 0, st, a); break;
+        case 7: hipLaunchKernelGGL((k_sweep_short<K, S, 7, Q, F>), grid, block, 0, st, a); break;
+        default: hipLaunchKernelGGL((k_sweep_short<K, S, 8, Q, F>), grid, block, 0, st, a); break;
     }
 }
 
@@ -1753,11 +1874,13 @@ static void launch_layout(ecc_matrix_t M, dim3 grid, dim3 block, hipStream_t st,
         if constexpr (!S) hipLaunchKernelGGL((k_sweep<K, S, kLayRanges>), grid, block, 0, st, a);
     } else if (M->layout == kLayShort) {
         if (M->queue) {
-            if (M->dia) launch_short<K, S, true, true>(M, grid, block, st, a);
-            else launch_short<K, S, true, false>(M, grid, block, st, a);
+            if (M->dia_const) launch_short<K, S, true, kFormDiaConst>(M, grid, block, st, a);
+            else if (M->dia) launch_short<K, S, true, kFormDia>(M, grid, block, st, a);
+            else launch_short<K, S, true, kFormGeneral>(M, grid, block, st, a);
         } else {
-            if (M->dia) launch_short<K, S, false, true>(M, grid, block, st, a);
-            else launch_short<K, S, false, false>(M, grid, block, st, a);
+            if (M->dia_const) launch_short<K, S, false, kFormDiaConst>(M, grid, block, st, a);
+            else if (M->dia) launch_short<K, S, false, kFormDia>(M, grid, block, st, a);
+            else launch_short<K, S, false, kFormGeneral>(M, grid, block, st, a);
         }
     } else {
         hipLaunchKernelGGL((k_sweep<K, S, kLayStream>), grid, block, 0, st, a);
@@ -1794,6 +1917,7 @@ ecc_status_t launch_sweep(ecc_matrix_t M, const SweepLaunch &L) {
     a.ell_val = M->d_ell_val;
     a.ell_mask = M->d_ell_mask;
     a.dia = M->dia_off;
+    a.dia_val = M->dia_val;
     a.ell_n = M->A.n_rows;
     a.interleave = M->irregular ? 1 : 0;
     // a queue-scheduled sweep needs no reserved workgroup: workgroup 0 takes
@@ -2114,7 +2238,10 @@ static ecc_status_t ecc_matrix_create_impl(ecc_plan_t plan, const ecc_csr_t *A, 
     std::vector<int32_t> order, srp;
     RangeBuild RB;
     int64_t tile_plane = 0, tile_rows = 0, short_rows_total = 0;
-    bool dia = false;  // short layout in diagonal form
+    // a small short-row problem is solved by one launch (tiny.hip)
+    bool tiny = false;
+    bool dia = false, dia_const = false;  // short layout in diagonal form, of constant diagonals
+    DiagValues dia_val{};
     int32_t n_dia = 0;
     DiagOffsets dia_off{};
     if (layout == kLayRanges) {
@@ -2218,6 +2345,43 @@ static ecc_status_t ecc_matrix_create_impl(ecc_plan_t plan, const ecc_csr_t *A, 
                 for (int k = 0; k < kDiagMax; ++k) dia_off.v[k] = k < n_dia ? offs[k] : 0;
             }
         }
+        tiny = tiny_fits(n, std::max(1, max_row), (int64_t)items.size(), plan->P) &&
+               (opts.schedule == ECC_SCHEDULE_AUTO || opts.schedule == ECC_SCHEDULE_SINGLE);
+        // (the single-launch solve keeps its rows' values in registers)
+        if (dia && !tiny) {
+            const int blocks = (int)std::min<int64_t>(2048, (n + 255) / 256);
+            std::vector<unsigned long long> h_rep((size_t)blocks * kDiagMax);
+            std::vector<uint32_t> h_have(blocks + 1);  // and the bad flag
+            unsigned long long *d_rep = nullptr;
+            uint32_t *d_have = nullptr;
+            hipError_t e = hipMalloc((void **)&d_rep, sizeof(h_rep[0]) * h_rep.size());
+            if (e == hipSuccess)
+                e = hipMalloc((void **)&d_have, sizeof(uint32_t) * h_have.size());
+            if (e == hipSuccess)
+                e = hipMemcpy(d_have, h_have.data(), sizeof(uint32_t) * h_have.size(),
+                              hipMemcpyHostToDevice);
+            if (e == hipSuccess) {
+                hipLaunchKernelGGL(k_diag_values, dim3(blocks), dim3(256), 0, plan->stream,
+                                   (int32_t)n, n_dia, dia_off, A->d_row_ptr, A->d_col, A->d_val,
+                                   d_rep, d_have, d_have + blocks);
+                e = hipGetLastError();
+                if (e == hipSuccess) e = hipStreamSynchronize(plan->stream);
+                if (e == hipSuccess)
+                    e = hipMemcpy(h_rep.data(), d_rep, sizeof(h_rep[0]) * h_rep.size(),
+                                  hipMemcpyDeviceToHost);
+                if (e == hipSuccess)
+                    e = hipMemcpy(h_have.data(), d_have, sizeof(uint32_t) * h_have.size(),
+                                  hipMemcpyDeviceToHost);
+            }
+            (void)hipFree(d_rep);
+            (void)hipFree(d_have);
+            if (e != hipSuccess) {
+                set_error("diagonal value check failed: %s", hipGetErrorString(e));
+                return e == hipErrorOutOfMemory ? ECC_ERR_ALLOC : ECC_ERR_DEVICE;
+            }
+            dia_const = h_have[blocks] == 0 &&
+                        merge_diag_values(blocks, h_rep.data(), h_have.data(), dia_val);
+        }
     } else {
         build_items(rp, plan->counts, nullptr, items, fixups, n_pieces);
     }
@@ -2243,8 +2407,10 @@ static ecc_status_t ecc_matrix_create_impl(ecc_plan_t plan, const ecc_csr_t *A, 
     M->bandwidth = bandwidth;
     M->tile_plane = tile_plane;
     M->tile_rows = tile_rows;
-    M->grid = sweep_grid(M->n_items, kind, layout, M->short_r, colscale, dia);
+    M->grid = sweep_grid(M->n_items, kind, layout, M->short_r, colscale, kFormGeneral);
     M->dia = dia;
+    M->dia_const = dia_const;
+    M->dia_val = dia_val;
     M->n_dia = n_dia;
     M->dia_off = dia_off;
     M->colscale = colscale;
@@ -2260,9 +2426,14 @@ static ecc_status_t ecc_matrix_create_impl(ecc_plan_t plan, const ecc_csr_t *A, 
     // A small short-row problem is solved by one launch (tiny.hip), whose
     // norm reduces one partial per row: its sweeps write per-row partials
     // too, so that every entry point gives the same norm.
-    M->tiny = layout == kLayShort && tiny_fits(n, M->short_r, M->n_items, plan->P) &&
-              (opts.schedule == ECC_SCHEDULE_AUTO || opts.schedule == ECC_SCHEDULE_SINGLE);
+    M->tiny = tiny;
     if (M->tiny) M->queue = false;
+    // The static walk keeps the general form's grid, and with it the partial
+    // norms; items claimed from the queue have a partial each, so that there
+    // the grid follows the registers of the form's own kernel.
+    if (M->queue && dia)
+        M->grid = sweep_grid(M->n_items, kind, layout, M->short_r, colscale,
+                             dia_const ? kFormDiaConst : kFormDia);
     M->n_part = M->tiny ? n + 1 : M->queue ? M->n_items + 1 : (int64_t)M->grid + 1;
     auto fail = [&](const char *what) {
         set_error("%s", what);
@@ -2339,7 +2510,8 @@ static ecc_status_t ecc_matrix_create_impl(ecc_plan_t plan, const ecc_csr_t *A, 
         if ((dia ? hipMalloc((void **)&M->d_ell_mask, short_rows_total)
                  : hipMalloc((void **)&M->d_ell_col, sizeof(int32_t) * R * short_rows_total)) !=
                 hipSuccess ||
-            hipMalloc((void **)&M->d_ell_val, sizeof(double) * R * short_rows_total) != hipSuccess)
+            (!dia_const && hipMalloc((void **)&M->d_ell_val,
+                                     sizeof(double) * R * short_rows_total) != hipSuccess))
             return fail("hipMalloc of the item-major entries failed");
         const int blocks = (int)std::min<int64_t>(65536, M->n_items);
         if (dia)
@@ -2451,6 +2623,17 @@ ecc_status_t ecc_matrix_form(ecc_matrix_t M, int32_t *form, int32_t *n_diagonals
     if (offsets)
         for (int k = 0; k < ECC_MAX_DIAGONALS; ++k)
             offsets[k] = (M->dia && k < M->n_dia) ? M->dia_off.v[k] : 0;
+    return ECC_OK;
+}
+
+ecc_status_t ecc_matrix_diagonal_values(ecc_matrix_t M, int32_t *constant, double *values) {
+    clear_error();
+    ECC_ARG(M != nullptr, "matrix is NULL");
+    ECC_ARG(constant != nullptr, "NULL output");
+    *constant = M->dia_const ? 1 : 0;
+    if (values)
+        for (int k = 0; k < ECC_MAX_DIAGONALS; ++k)
+            values[k] = (M->dia_const && k < M->n_dia) ? M->dia_val.v[k] : 0.0;
     return ECC_OK;
 }
 

@@ -990,6 +990,65 @@ def test_diagonal_form_matches_general_form(which):
         assert np.array_equal(u, v)
 
 
+def _constant_diagonals(prob, offsets, values):
+    """prob with every entry of diagonal offsets[k] set to values[k]."""
+    rows = np.repeat(np.arange(prob.n), np.diff(prob.A.row_ptr))
+    at = np.searchsorted(np.array(offsets), prob.A.col - rows)
+    return dataclasses.replace(prob, A=W.CSR(prob.n, prob.n, prob.A.row_ptr, prob.A.col,
+                                             np.array(values)[at]))
+
+
+@pytest.mark.parametrize("kind,offsets,n,P,schedule", [
+    ("jacobi", [-1, 0, 1], 70001, 13, "AUTO"),
+    ("jacobi", [-700, -3, -1, 0, 2, 650, 1800], 20011, 9, "AUTO"),
+    ("jacobi", [-900, -30, -1, 0, 1, 30, 900], 20011, 300, "QUEUE"),
+    ("jacobi", [-64, -1, 0, 1, 64], 700, 2, "STATIC"),
+    ("power", [-1500, -40, -2, -1, 0, 1, 40, 1500], 9999, 5, "QUEUE"),
+    ("power", [3, 7, 60], 3001, 3, "STATIC"),
+])
+def test_constant_diagonals(kind, offsets, n, P, schedule):
+    """One value per diagonal, rows holding random subsets of the diagonals
+    (power rows possibly none): the values are found and no longer read by
+    row; iterates, assembled vector and norms are the oracle's and, bit for
+    bit, the general form's.  One entry an ulp off, in the first, a middle or
+    the last row, and the values go by row again."""
+    E = _capi()
+    announce("constant diagonals", kind, offsets, n, P, schedule)
+    values = [(-1.0) ** k / (3.0 + k) / 8.0 for k in range(len(offsets))]
+    if kind == "jacobi":
+        values[offsets.index(0)] = 2.5
+    else:
+        values = [abs(v) for v in values]
+    kw = {"schedule": getattr(E, "ECC_SCHEDULE_" + schedule)}
+    prob = _constant_diagonals(_offset_subset_problem(kind, n, offsets, P, seed=n + P), offsets,
+                               values)
+    run = _iterative(prob, **kw)
+    assert E.ecc_matrix_diagonal_values(run.mat) == values
+    run.close()
+    _solve_and_compare(prob, bitwise=True, form=E.ECC_FORM_DIAGONALS, solves=2, **kw)
+    outs = []
+    for compact in (E.ECC_COMPACT_AUTO, E.ECC_COMPACT_NONE):
+        run = _iterative(prob, compact=compact, **kw)
+        assert (E.ecc_matrix_diagonal_values(run.mat) is None) == (compact == E.ECC_COMPACT_NONE)
+        run.solve(histories=True)
+        torch.cuda.synchronize()
+        outs.append((run.d_x.cpu().numpy(), run.d_x_hat.cpu().numpy(),
+                     run.d_rho.cpu().numpy()[:prob.T]))
+        run.close()
+    for u, v in zip(*outs):
+        assert np.array_equal(u, v)
+    _step_api_matches_solve((prob,), schedule=kw["schedule"])
+    nnz = int(prob.A.row_ptr[-1])
+    for k in (0, nnz // 2, nnz - 1):
+        val = prob.A.val.copy()
+        val[k] = np.nextafter(val[k], 9.0)
+        bent = dataclasses.replace(prob, A=W.CSR(n, n, prob.A.row_ptr, prob.A.col, val))
+        run = _iterative(bent, **kw)
+        assert E.ecc_matrix_form(run.mat)[0] == E.ECC_FORM_DIAGONALS
+        assert E.ecc_matrix_diagonal_values(run.mat) is None
+        run.close()
+
+
 @pytest.mark.parametrize("kind", ["jacobi", "power"])
 @pytest.mark.parametrize("counts", [[20000], [0, 3000, 0, 9000, 1000, 7000], 9])
 def test_solve_sorted_layout(kind, counts):
