@@ -571,6 +571,18 @@ def test_solve_stream_layout(kind, lmin, lmax):
     _solve_and_compare(_banded_problem(kind, 30000, lmin, lmax), bitwise=(lmax <= 16))
 
 
+@pytest.mark.parametrize("kind,lmin,lmax,n,P", [
+    ("jacobi", 9, 9, 2003, 400), ("jacobi", 15, 17, 2003, 1), ("power", 0, 33, 5003, 7),
+    ("jacobi", 64, 64, 700, 3), ("power", 9, 16, 2049, 2), ("jacobi", 2, 48, 3001, 30)])
+def test_stream_rows_around_the_unroll(kind, lmin, lmax, n, P):
+    """Stream items of ranks of a few rows, one rank, rows of exactly and
+    around eight entries per lane, empty rows (power), and the diagonal entry
+    anywhere in the row: the loop and the separate calls."""
+    prob = _banded_problem(kind, n, lmin, lmax, P=P, T=12)
+    _solve_and_compare(prob, bitwise=(lmax <= 16), layout="STREAM")
+    _step_api_matches_solve((prob,))
+
+
 @pytest.mark.parametrize("kind,lmin,lmax", [
     ("jacobi", 1, 2), ("power", 0, 3), ("jacobi", 2, 4), ("power", 3, 6), ("jacobi", 5, 7),
     ("jacobi", 8, 8), ("power", 1, 8)])
