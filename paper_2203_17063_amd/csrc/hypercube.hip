@@ -33,6 +33,20 @@ namespace ecc {
 __device__ __forceinline__ void hc_st(double *p, double v) { __builtin_nontemporal_store(v, p); }
 __device__ __forceinline__ double hc_ld(const double *p) { return __builtin_nontemporal_load(p); }
 
+// Two neighbouring elements of a row by one 16-byte access at any 8-byte
+// alignment; a row's last element alone where m is odd (live = 1).
+typedef WordVec<2>::t HcPair;
+__device__ __forceinline__ HcPair hc_ld2(const double *p, int live) {
+    HcPair v = HcPair(0.0);
+    if (live == 2) v = __builtin_nontemporal_load((GlobalPtr<const HcPair>)p);
+    else if (live == 1) v.x = hc_ld(p);
+    return v;
+}
+__device__ __forceinline__ void hc_st2(double *p, HcPair v, int live) {
+    if (live == 2) __builtin_nontemporal_store(v, (GlobalPtr<HcPair>)p);
+    else if (live == 1) hc_st(p, v.x);
+}
+
 constexpr int kHcThreads = 256;
 constexpr int kHcMaxDims = 5;  // P <= 32: one launch, one lane per process in the scalar phase
 constexpr int kHcMaxDimsBig = 12;  // P <= 4096: decisions, sub-cubes, then step by step
@@ -143,7 +157,7 @@ __global__ __launch_bounds__(kHcThreads) void k_allreduce_ssp(HcArgs a) {
 }
 
 // Split layout, for 8 to 32 processes and for the 32-process sub-cubes of
-// larger calls: the 2^D partials of element j are held by the W = 2^LW
+// larger calls: the 2^D partials of a pair of elements are held by the W = 2^LW
 // waves of a workgroup, 2^D / W each (wave w holds processes w 2^D / W + i),
 // so that every decision stays uniform in a wave and a thread holds few
 // partials.  Steps 0 .. D-LW-1 pair processes within a wave; each of the
@@ -153,16 +167,18 @@ __global__ __launch_bounds__(kHcThreads) void k_allreduce_ssp(HcArgs a) {
 // blockIdx.y selects the sub-cube of processes 2^D y .. 2^D (y + 1) - 1,
 // whose fresh flags for steps 0 .. D-1 come from fresh_in, and the partials
 // go to the result for the remaining steps.  Measured on MI355X (32
-// processes x 16 MB, slack 2, 80 % delivery): 789 us per call with four
-// waves (50 VGPRs, 8 waves per SIMD), 885 us with two (90 VGPRs), 827 us
-// with eight, against 937 us with the 32 partials in one thread.
+// processes x 16 MB, slack 2, 80 % delivery): 735 us per call (5.1 TB/s) with
+// two elements, 16 bytes, per lane (78 VGPRs, four workgroups per CU by LDS;
+// exchanging half of the partials at a time, five, measured the same), 780 us
+// with one.  By waves, at one element per lane: 789 us with four, 885 us with
+// two, 827 us with eight, against 937 us with the 32 partials in one thread.
 template <int D, int LW, bool CUBE>
 __global__ __launch_bounds__(64 << LW) void k_allreduce_ssp_split(HcArgs a,
                                                                   const uint8_t *__restrict__ fresh_in) {
     constexpr int Pt = 1 << D, W = 1 << LW, H = Pt / W;
     static_assert(LW >= 1 && LW < D && D <= kHcMaxDims, "a split of at most 32 processes");
     __shared__ unsigned long long s_fresh[kHcMaxDims];
-    __shared__ double s_x[W][H][64];
+    __shared__ HcPair s_x[W][H][64];
     const int32_t pc = CUBE ? (int32_t)blockIdx.y * Pt : 0;  // the sub-cube's first process
     if constexpr (CUBE) {
         if (threadIdx.x < 64) {
@@ -184,14 +200,14 @@ __global__ __launch_bounds__(64 << LW) void k_allreduce_ssp_split(HcArgs a,
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t m = a.m;
     const int64_t sd = CUBE ? (int64_t)a.D : D;  // slots per process
-    const int64_t j = (int64_t)blockIdx.x * 64 + lane;
-    const bool live = j < m;
+    const int64_t j = 2 * ((int64_t)blockIdx.x * 64 + lane);
+    const int live = j + 1 < m ? 2 : j < m ? 1 : 0;  // elements of this lane
     const int p0 = wv * H;  // this wave's first process in the (sub-)cube
     auto slot = [&](int i, int k) { return a.slots + ((int64_t)(pc + p0 + i) * sd + k) * m + j; };
-    double part[H];
+    HcPair part[H];
 #pragma unroll
     for (int i = 0; i < H; ++i)
-        part[i] = live ? hc_ld(a.contrib + (int64_t)(pc + p0 + i) * m + j) : 0.0;
+        part[i] = hc_ld2(a.contrib + (int64_t)(pc + p0 + i) * m + j, live);
 #pragma unroll
     for (int k = 0; k < D - LW; ++k) {
         const int bit = 1 << k;
@@ -201,10 +217,10 @@ __global__ __launch_bounds__(64 << LW) void k_allreduce_ssp_split(HcArgs a,
             const int q = i | bit;
             const bool fr = (fresh[k] >> (p0 + i)) & 1ull, fq = (fresh[k] >> (p0 + q)) & 1ull;
             double *sr = slot(i, k), *sq = slot(q, k);
-            const double gr = fr ? part[q] : (live ? hc_ld(sr) : 0.0);
-            const double gq = fq ? part[i] : (live ? hc_ld(sq) : 0.0);
-            if (fr && live) hc_st(sr, gr);
-            if (fq && live) hc_st(sq, gq);
+            const HcPair gr = fr ? part[q] : hc_ld2(sr, live);
+            const HcPair gq = fq ? part[i] : hc_ld2(sq, live);
+            if (fr) hc_st2(sr, gr, live);
+            if (fq) hc_st2(sq, gq, live);
             part[i] = part[i] + gr;
             part[q] = part[q] + gq;
         }
@@ -220,16 +236,15 @@ __global__ __launch_bounds__(64 << LW) void k_allreduce_ssp_split(HcArgs a,
         for (int i = 0; i < H; ++i) {
             const bool fr = (fresh[k] >> (p0 + i)) & 1ull;
             double *sr = slot(i, k);
-            const double gr = fr ? s_x[pw][i][lane] : (live ? hc_ld(sr) : 0.0);
-            if (fr && live) hc_st(sr, gr);
+            const HcPair gr = fr ? s_x[pw][i][lane] : hc_ld2(sr, live);
+            if (fr) hc_st2(sr, gr, live);
             part[i] = part[i] + gr;
         }
         if (k + 1 < D) __syncthreads();  // every partner read before the next writes
     }
-    if (live) {
 #pragma unroll
-        for (int i = 0; i < H; ++i) hc_st(a.result + (int64_t)(pc + p0 + i) * m + j, part[i]);
-    }
+    for (int i = 0; i < H; ++i)
+        hc_st2(a.result + (int64_t)(pc + p0 + i) * m + j, part[i], live);
 }
 
 // More than 32 processes.  One call is then three kinds of launch:
@@ -343,11 +358,11 @@ void hc_launch(dim3 grid, hipStream_t st, const HcArgs &a) {
     hipLaunchKernelGGL((k_allreduce_ssp<D>), grid, dim3(kHcThreads), 0, st, a);
 }
 
-constexpr int kHcSplitLW = 2;  // four waves per 64 elements
+constexpr int kHcSplitLW = 2;  // four waves per 128 elements
 
 template <int D>
 void hc_launch_split(int64_t m, hipStream_t st, const HcArgs &a) {
-    const int64_t g = std::max<int64_t>(1, (m + 63) / 64);
+    const int64_t g = std::max<int64_t>(1, (m + 127) / 128);
     hipLaunchKernelGGL((k_allreduce_ssp_split<D, kHcSplitLW, false>), dim3((unsigned)g),
                        dim3(64 << kHcSplitLW), 0, st, a, nullptr);
 }
@@ -473,7 +488,7 @@ ecc_status_t ecc_allreduce_ssp(ecc_hypercube_t h, const double *d_contrib,
         hipLaunchKernelGGL(k_hc_decide_big, dim3(1), dim3(kHcDecideThreads), 0, h->stream, a,
                            h->d_fresh);
         ECC_LAUNCH_CHECK();
-        const int64_t g = std::max<int64_t>(1, (h->m + 63) / 64);
+        const int64_t g = std::max<int64_t>(1, (h->m + 127) / 128);
         hipLaunchKernelGGL((k_allreduce_ssp_split<kHcCubeDims, kHcSplitLW, true>),
                            dim3((unsigned)g, h->P >> kHcCubeDims), dim3(64 << kHcSplitLW), 0,
                            h->stream, a, h->d_fresh);

@@ -79,6 +79,15 @@ def test_parity_ragged_lengths(m):
     _run_and_compare(32, m, 1, 0.6, T=8, seed=m)
 
 
+@pytest.mark.parametrize("P", [8, 32, 64])
+@pytest.mark.parametrize("m", [2, 63, 127, 128, 129, 255, 257])
+def test_parity_pairs(P, m):
+    """Two elements per lane, 128 per workgroup: lengths around the tile, a
+    last element without a partner, rows at odd multiples of 8 bytes, and
+    every call in place."""
+    _run_and_compare(P, m, 1, 0.6, T=5, seed=P + m, in_place=True)
+
+
 @pytest.mark.parametrize("P,m,slack,q,in_place", [
     (128, 700, 1, 0.6, False),
     (256, 257, 2, 0.5, True),
