@@ -179,6 +179,15 @@ __device__ __forceinline__ uint64_t wave_uniform(uint64_t x) {
     return (uint64_t)lo | ((uint64_t)hi << 32);
 }
 
+// Workgroup barrier for data exchanged through LDS only: waits for this
+// wave's LDS operations, not for its global loads and stores (which
+// __syncthreads' fence would drain at every barrier: the arrival flags
+// prefetched for the next iteration, the norms and histories written).  The
+// memory clobber keeps the compiler from moving accesses across it.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // 64-bit lane exchange through two 32-bit DPP moves.
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {
@@ -310,19 +319,22 @@ __device__ __forceinline__ void record_step(int32_t P, int32_t S, int64_t t,
 
 // Row epilogue of the block-row iterations; returns the row's contribution
 // to the norm (r_i^2 for Jacobi, |x_next_j - x_own_j| for the power step).
-template <int KIND>
+// STREAM: x_next passes L2 by.
+template <int KIND, bool STREAM = false>
 __device__ __forceinline__ double row_finish(int32_t i, double s, double dg, double bi,
                                              double xo, double alpha, double beta,
                                              double *__restrict__ x_next) {
     if constexpr (KIND == ECC_KIND_JACOBI) {
         const double bs = bi - s;
         const double xn = bs / dg;
-        x_next[i] = xn;
+        if constexpr (STREAM) __builtin_nontemporal_store(xn, x_next + i);
+        else x_next[i] = xn;
         const double r = bs - dg * xo;
         return r * r;
     } else {
         const double xn = alpha * s + beta;
-        x_next[i] = xn;
+        if constexpr (STREAM) __builtin_nontemporal_store(xn, x_next + i);
+        else x_next[i] = xn;
         return fabs(xn - xo);
     }
 }
@@ -429,6 +441,7 @@ struct ecc_matrix_s {
     int64_t n_rfix = 0;
     int32_t *d_ell_col = nullptr;   // short layout: entries item by item, entry-major (-1: padding)
     uint8_t *d_ell_mask = nullptr;  // short layout, diagonal form: the diagonals each row holds
+    uint16_t *d_dia_rank = nullptr;  // queue: the rank of each item's columns by diagonal
     bool dia = false;               // short layout in diagonal form (d_ell_mask, no d_ell_col)
     int32_t n_dia = 0;              // its diagonals
     ecc::DiagOffsets dia_off{};     // their offsets, ascending

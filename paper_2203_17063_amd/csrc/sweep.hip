@@ -93,6 +93,8 @@ struct SweepArgs {
     const uint8_t *ell_mask;  // short layout, diagonal form: the diagonals of each row
     DiagOffsets dia;          // and their offsets
     DiagValues dia_val;       // constant diagonals: the value of each
+    const uint16_t *dia_rank; // queue over them: [n_items][kDiagMax] the rank of an item's
+                              // columns, or null
     int64_t ell_n;
     int32_t interleave;  // items dealt round-robin instead of in XCD ranges
     int32_t reserve0;    // workgroup 0 takes no items (grids of kReserveMinGrid or more)
@@ -916,7 +918,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_range_finish(RangeFinishArgs
 // stored values, bit for bit.  Measured on MI355X (Jacobi on the 400^3
 // 7-point stencil, 512 ranks): 845 us per iteration against 1,246 with the
 // value planes.
-enum { kFormGeneral = 0, kFormDia = 1, kFormDiaConst = 2 };
+enum { kFormGeneral = 0, kFormDia = 1, kFormDiaConst = 2, kFormDiaPipe = 3 };
 
 template <int R, int FORM>
 struct EllEntries {
@@ -1074,6 +1076,17 @@ __device__ __forceinline__ int32_t queue_take(unsigned *q, int64_t n_items, int 
     return -1;
 }
 
+// The last workgroup out zeroes the counters for the next launch.
+__device__ __forceinline__ void queue_finish(const SweepArgs &a, int tid) {
+    if (tid == 0) {
+        unsigned *fin = a.queue + kQueueRanges * kQueueStride;
+        if (atomicAdd(fin, 1u) == gridDim.x - 1) {
+            for (int q = 0; q < kQueueRanges; ++q) atomicExch(a.queue + q * kQueueStride, 0u);
+            atomicExch(fin, 0u);
+        }
+    }
+}
+
 // The hardware id of the XCD running the calling wave (HW_REG_XCC_ID, bits
 // 3:0): a read of a hardware register.
 __device__ __forceinline__ int xcc_id() {
@@ -1163,14 +1176,273 @@ __device__ __forceinline__ void short_body_queue(const SweepArgs &a) {
         nxt = nn;
         E = En;
     }
-    // the last workgroup out zeroes the counters for the next launch
-    if (tid == 0) {
-        unsigned *fin = a.queue + kQueueRanges * kQueueStride;
-        if (atomicAdd(fin, 1u) == gridDim.x - 1) {
-            for (int q = 0; q < kQueueRanges; ++q) atomicExch(a.queue + q * kQueueStride, 0u);
-            atomicExch(fin, 0u);
+    queue_finish(a, tid);
+}
+
+// Constant diagonals: where an item's columns on each diagonal lie, one entry per
+// diagonal: kRankOwn (its own block, or no such diagonal), one other rank, or
+// kRankMixed (several ranks, or rows outside the matrix).
+constexpr uint16_t kRankMixed = 0xffff, kRankOwn = 0xfffe;
+
+__global__ void k_dia_ranks(int64_t n_items, int32_t n, int32_t D, DiagOffsets off, int32_t P,
+                            const int32_t *__restrict__ block_start,
+                            const WorkItem *__restrict__ items, uint16_t *__restrict__ rank) {
+    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n_items * kDiagMax;
+         x += (int64_t)gridDim.x * blockDim.x) {
+        const WorkItem it = items[x / kDiagMax];
+        const int32_t j = (int32_t)(x % kDiagMax);
+        uint16_t r = kRankOwn;
+        if (j < D) {
+            const int64_t c0 = (int64_t)it.row0 + off.v[j], c1 = c0 + it.nrows - 1;
+            r = kRankMixed;
+            if (c0 >= it.lo && c1 < it.hi) {
+                r = kRankOwn;
+            } else if (c0 >= 0 && c1 < n) {
+                int32_t a = 0, z = P;  // block_start[a] <= c0 < block_start[z]
+                while (z - a > 1) {
+                    const int32_t mid = (a + z) >> 1;
+                    if (block_start[mid] <= c0) a = mid;
+                    else z = mid;
+                }
+                if (c1 < block_start[a + 1] && a < kRankOwn) r = (uint16_t)a;
+            }
         }
+        rank[x] = r;
     }
+}
+
+__device__ __forceinline__ int32_t uniform32(int32_t v) {
+    return __builtin_amdgcn_readfirstlane(v);
+}
+
+// An item's descriptor, read by a workgroup as one, in scalar registers.
+__device__ __forceinline__ WorkItem uniform_item(const WorkItem &v) {
+    WorkItem u = v;
+    u.row0 = uniform32(v.row0);
+    u.nrows = uniform32(v.nrows);
+    u.k0 = uniform32(v.k0);
+    u.lo = uniform32(v.lo);
+    u.hi = uniform32(v.hi);
+    u.rank = uniform32(v.rank);
+    return u;
+}
+
+// The launch's arguments, through a pointer the compiler cannot follow from
+// one item to the next: an item's body then loads the ones it uses into
+// scalar registers (one cached scalar load each), where the arguments kept
+// over the loop overflow them (up to 150 spilled to vector lanes, one vector
+// instruction per use).
+typedef const __attribute__((address_space(4))) SweepArgs *KernArgs;
+__device__ __forceinline__ KernArgs kernel_args() {
+    return (KernArgs)__builtin_amdgcn_kernarg_segment_ptr();
+}
+__device__ __forceinline__ const SweepArgs &item_args(KernArgs &k) {
+    asm volatile("" : "+s"(k));
+    return *(const SweepArgs *)k;
+}
+
+// The queue over constant diagonals, gathers one item ahead.  A row holds a
+// byte of the matrix there, so registers are left for a second set of
+// gathers: while item n is finished, the gathers of item n + 1, the masks of
+// n + 2 and the descriptor of n + 3 are in flight, and a ticket is looked at
+// in the iteration after the one that draws it.  Loads and stores retire
+// through one in-order counter, so the order of issue is what an item waits
+// for: masks before gathers, and nothing else between.  The vectors an item
+// reads or writes once (b, x_next, x_hat) are non-temporal, which keeps x in
+// L2 for the neighbouring planes (4 % at 400^3).  Bound by latency: about 34
+// bytes and 154 vector instructions per row of 64 lanes use 60 % of the
+// memory's rate and a third of the issue slots.
+// Measured on MI355X, us per iteration, with short_body_queue / with the
+// gathers ahead / and 4 items to a ticket (2: 649, 8: 647 at 400^3):
+//   400^3, 512 ranks        851 / 694 / 642
+//   250 x 251 x 249, 100    230 / 208 / 183
+//   6001 x 5999, 32         412 / 400 / 342
+//   3001 x 2999, 32         137 / 137 / 105
+//   20,000,001 in a line    244 / 233 / 178
+template <int R>
+struct ShortGathers {
+    double y[R];
+    double xo, bi;
+    uint32_t mk;
+    bool whole;
+};
+
+// One item's mask and, in lanes k < kDiagMax, the rank of its columns on
+// diagonal k (lanes past the item's rows read its last row's mask).
+struct ShortMasks {
+    uint32_t mk, rk;
+};
+__device__ __forceinline__ ShortMasks pipe_masks(const SweepArgs &a, int32_t w, const WorkItem &it,
+                                                 int tid) {
+    ShortMasks m;
+    m.mk = (a.ell_mask + it.k0)[min(tid, it.nrows - 1)];
+    m.rk = (a.dia_rank + (int64_t)w * kDiagMax)[tid & (kDiagMax - 1)];
+    return m;
+}
+
+// The gathers of an item (nrows >= 1).  Where every lane of the wave holds a
+// row with all diagonals, and the columns of each lie in one rank's block, a
+// diagonal's 64 columns are consecutive elements of one vector: its base is
+// uniform, and neither the rank of each column nor a row's mask is looked at
+// (most waves of a stencil).  Compiled for R diagonals, Jacobi's main one in
+// their middle, as stencils have them (a.dia_rank is null for other sets,
+// which take short_body_queue).
+template <int KIND, bool STEP, int R>
+__device__ __forceinline__ void pipe_gather(const SweepArgs &a, const WorkItem &w, int tid,
+                                            const ShortMasks &m, const uint8_t *s_eff,
+                                            const StepView &sv, RankCache &rc,
+                                            ShortGathers<R> &g) {
+    const bool live = tid < w.nrows;
+    g.mk = live ? m.mk : 0u;
+    g.whole = __ballot(g.mk != (1u << R) - 1u || m.rk == kRankMixed) == 0;
+    if (g.whole) {
+        bool own = m.rk == kRankOwn;
+        if constexpr (STEP) own = own || s_eff[min(m.rk, (uint32_t)kFusedMaxP - 1)] != 0;
+        const uint32_t owns = (uint32_t)__ballot(own);  // lanes j < kDiagMax: diagonal j
+        const double *const x_own = a.x_own + w.row0, *const x_hat = a.x_hat + w.row0;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            if (KIND == ECC_KIND_JACOBI && j == R / 2) continue;  // (summed apart)
+            const double *x = (((owns >> j) & 1u) ? x_own : x_hat) + a.dia.v[j];
+            g.y[j] = x[tid];
+        }
+    } else {
+        const int32_t i = w.row0 + tid;
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+            g.y[j] = (((g.mk >> j) & 1u) && !(KIND == ECC_KIND_JACOBI && j == R / 2))
+                         ? view_load<STEP>(i + a.dia.v[j], w.lo, w.hi, a.x_own, a.x_hat, sv, rc)
+                         : 0.0;
+        // All of them arrived: the loads in flight after this branch are then
+        // known, and the waits that follow do not assume the fewest.
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+    }
+    const int32_t l = min(tid, w.nrows - 1);
+    g.xo = (a.x_own + w.row0)[l];
+    g.bi = 0.0;
+    if constexpr (KIND == ECC_KIND_JACOBI) g.bi = __builtin_nontemporal_load(a.b + w.row0 + l);
+}
+
+// Thread 0's share of the queue: a ticket stands for kTicketItems consecutive
+// items of its range, and the next one is drawn when it is begun and looked at
+// when its items have been handed out.  (One atomic per item bounded the
+// sweep: 22 ns each on one range's counter, whatever the stencil.)
+constexpr int32_t kTicketItems = 4;
+struct TicketWalk {
+    int r, left;          // the range, and how many are left
+    int32_t at, end;      // items of the current ticket
+    unsigned drawn;
+    __device__ __forceinline__ void begin(unsigned *q, int range) {
+        r = range;
+        left = kQueueRanges;
+        at = end = 0;
+        drawn = atomicAdd(&q[r * kQueueStride], 1u);
+    }
+    __device__ __forceinline__ int32_t next(unsigned *q, int64_t n_items) {
+        if (at < end) return at++;
+        while (left > 0) {
+            const int64_t b = n_items * r / kQueueRanges, e = n_items * (r + 1) / kQueueRanges;
+            const int64_t k = b + (int64_t)drawn * kTicketItems;
+            const bool have = k < e;
+            if (have) {
+                at = (int32_t)k;
+                end = (int32_t)min(e, k + kTicketItems);
+            } else {
+                r = (r + 1) % kQueueRanges;
+                --left;
+            }
+            if (left > 0) drawn = atomicAdd(&q[r * kQueueStride], 1u);
+            if (have) return at++;
+        }
+        return -1;
+    }
+};
+
+template <int KIND, bool STEP, int R>
+__device__ __forceinline__ void short_body_pipe(const SweepArgs &a) {
+    __shared__ double s_red[kSweepThreads / 64];
+    __shared__ double s_ws[2][kSweepThreads / 64];
+    __shared__ int32_t s_tk[6];  // [0..1] tickets handed on per item, [2..5] the first four
+    __shared__ uint8_t s_eff[STEP ? kFusedMaxP : 1];
+    __shared__ int32_t s_bs[STEP ? kFusedMaxP + 1 : 1];
+    if (a.done && *a.done) return;
+    const int tid = threadIdx.x;
+    TicketWalk tickets{};
+    if (tid == 0) {
+        tickets.begin(a.queue, xcc_id() % kQueueRanges);
+        for (int k = 0; k < 4; ++k) s_tk[2 + k] = tickets.next(a.queue, a.n_items);
+    }
+    StepView sv{s_eff, s_bs, a.P};
+    sweep_prologue<STEP>(a, s_eff, s_bs, s_red);
+    __syncthreads();
+    int32_t w0 = uniform32(s_tk[2]), w1 = uniform32(s_tk[3]), w2 = uniform32(s_tk[4]),
+            w3 = uniform32(s_tk[5]);
+    // (where there is no further item, the loads ahead read the last one)
+    const int32_t last = (int32_t)a.n_items - 1;
+    auto item = [&](int32_t w) { return uniform_item(a.items[w >= 0 ? w : last]); };
+    WorkItem i0 = item(w0), i1 = item(w1), i2 = item(w2);
+    ShortMasks m1 = pipe_masks(a, w1 >= 0 ? w1 : last, i1, tid);
+    RankCache rc;
+    ShortGathers<R> G0;
+    pipe_gather<KIND, STEP, R>(a, i0, tid, pipe_masks(a, w0 >= 0 ? w0 : last, i0, tid), s_eff, sv,
+                               rc, G0);
+    int kk = 0;
+    KernArgs kargs = kernel_args();
+    while (w0 >= 0) {
+        const SweepArgs &a = item_args(kargs);
+        int32_t tk = -1;
+        if (tid == 0) tk = tickets.next(a.queue, a.n_items);
+        const WorkItem i3 = a.items[w3 >= 0 ? w3 : last];
+        const ShortMasks m2 = pipe_masks(a, w2 >= 0 ? w2 : last, i2, tid);
+        ShortGathers<R> G1;
+        pipe_gather<KIND, STEP, R>(a, i1, tid, m1, s_eff, sv, rc, G1);
+        double s = 0.0, dg = 0.0;
+        if (G0.whole) {
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                if (KIND == ECC_KIND_JACOBI && j == R / 2) dg = a.dia_val.v[j];
+                else s = s + a.dia_val.v[j] * G0.y[j];
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                if ((G0.mk >> j) & 1u) {
+                    if (KIND == ECC_KIND_JACOBI && j == R / 2) dg = a.dia_val.v[j];
+                    else s = s + a.dia_val.v[j] * G0.y[j];
+                }
+            }
+        }
+        double c = 0.0;
+        if (tid < i0.nrows) {
+            if (STEP && s_eff[i0.rank] != 0)
+                __builtin_nontemporal_store(G0.xo, a.x_hat + i0.row0 + tid);
+            c = row_finish<KIND, true>(tid, s, dg, G0.bi, G0.xo, a.alpha, a.beta,
+                                     a.x_next + i0.row0);
+        }
+        c = group_sum<64>(c);
+        const int slot = kk & 1;
+        if ((tid & 63) == 0) s_ws[slot][tid >> 6] = c;
+        if (tid == 0) s_tk[slot] = tk;
+        lds_barrier();
+        if (tid == 0) {
+            double t = s_ws[slot][0];
+#pragma unroll
+            for (int q = 1; q < kSweepThreads / 64; ++q) t += s_ws[slot][q];
+            a.partials[w0] = t;
+        }
+        const int32_t w4 = uniform32(s_tk[slot]);
+        ++kk;
+        w0 = w1;
+        w1 = w2;
+        w2 = w3;
+        w3 = w4;
+        i0 = i1;
+        i1 = i2;
+        i2 = uniform_item(i3);
+        m1 = m2;
+        G0 = G1;
+    }
+    queue_finish(a, tid);
 }
 
 // Item-major copy of a matrix whose rows hold at most R entries (layout as
@@ -1205,13 +1477,16 @@ __global__ void k_build_ell(int64_t n_items, int32_t R, const WorkItem *__restri
 // spill).
 template <int R, int FORM>
 constexpr int short_waves() {
-    return R <= 4 || FORM == kFormDiaConst ? 8 : (R == 5 ? 7 : 5);
+    if (FORM == kFormDiaPipe) return R >= 7 ? 7 : 8;
+    if (FORM == kFormDiaConst) return 8;
+    return R <= 4 ? 8 : (R == 5 ? 7 : 5);
 }
 template <int KIND, bool STEP, int R, bool QUEUE, int FORM>
 __global__ __launch_bounds__(kSweepThreads)
 __attribute__((amdgpu_waves_per_eu(short_waves<R, FORM>())))
 void k_sweep_short(SweepArgs a) {
-    if constexpr (QUEUE) short_body_queue<KIND, STEP, R, FORM>(a);
+    if constexpr (FORM == kFormDiaPipe) short_body_pipe<KIND, STEP, R>(a);
+    else if constexpr (QUEUE) short_body_queue<KIND, STEP, R, FORM>(a);
     else short_body<KIND, STEP, R, FORM>(a);
 }
 
@@ -1992,7 +2267,8 @@ static void launch_layout(ecc_matrix_t M, dim3 grid, dim3 block, hipStream_t st,
         if constexpr (!S) hipLaunchKernelGGL((k_sweep<K, S, kLayRanges>), grid, block, 0, st, a);
     } else if (M->layout == kLayShort) {
         if (M->queue) {
-            if (M->dia_const) launch_short<K, S, true, kFormDiaConst>(M, grid, block, st, a);
+            if (M->d_dia_rank) launch_short<K, S, true, kFormDiaPipe>(M, grid, block, st, a);
+            else if (M->dia_const) launch_short<K, S, true, kFormDiaConst>(M, grid, block, st, a);
             else if (M->dia) launch_short<K, S, true, kFormDia>(M, grid, block, st, a);
             else launch_short<K, S, true, kFormGeneral>(M, grid, block, st, a);
         } else {
@@ -2036,6 +2312,7 @@ ecc_status_t launch_sweep(ecc_matrix_t M, const SweepLaunch &L) {
     a.ell_mask = M->d_ell_mask;
     a.dia = M->dia_off;
     a.dia_val = M->dia_val;
+    a.dia_rank = M->d_dia_rank;
     a.ell_n = M->A.n_rows;
     a.interleave = M->irregular ? 1 : 0;
     // a queue-scheduled sweep needs no reserved workgroup: workgroup 0 takes
@@ -2632,6 +2909,17 @@ static ecc_status_t ecc_matrix_create_impl(ecc_plan_t plan, const ecc_csr_t *A, 
                                      sizeof(double) * R * short_rows_total) != hipSuccess))
             return fail("hipMalloc of the item-major entries failed");
         const int blocks = (int)std::min<int64_t>(65536, M->n_items);
+        // the sets of diagonals short_body_pipe is compiled for
+        if (dia_const && M->queue && n_dia == R &&
+            (kind != ECC_KIND_JACOBI || dia_off.v[R / 2] == 0)) {
+            if (hipMalloc((void **)&M->d_dia_rank, sizeof(uint16_t) * kDiagMax * M->n_items) !=
+                hipSuccess)
+                return fail("hipMalloc of the items' column ranks failed");
+            const int rb = (int)std::min<int64_t>(8192, (M->n_items * kDiagMax + 255) / 256);
+            hipLaunchKernelGGL(k_dia_ranks, dim3(rb), dim3(256), 0, plan->stream, M->n_items,
+                               (int32_t)n, n_dia, dia_off, plan->P, plan->d_block_start,
+                               M->d_items, M->d_dia_rank);
+        }
         if (dia)
             hipLaunchKernelGGL(k_build_dia, dim3(blocks), dim3(kSweepThreads), 0, plan->stream,
                                M->n_items, (int32_t)R, n_dia, dia_off, M->d_items, A->d_row_ptr,
@@ -2696,6 +2984,7 @@ ecc_status_t ecc_matrix_destroy(ecc_matrix_t M) {
     (void)hipFree(M->d_rfix);
     (void)hipFree(M->d_ell_col);
     (void)hipFree(M->d_ell_mask);
+    (void)hipFree(M->d_dia_rank);
     (void)hipFree(M->d_ell_val);
     (void)hipFree(M->d_queue);
     (void)hipFree(M->d_cscale);

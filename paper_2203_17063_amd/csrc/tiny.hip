@@ -20,15 +20,6 @@
 
 namespace ecc {
 
-// Workgroup barrier for data exchanged through LDS only: waits for this
-// wave's LDS operations, not for its global loads and stores (which
-// __syncthreads' fence would drain at every barrier: the arrival flags
-// prefetched for the next iteration, the norms and histories written).  The
-// memory clobber keeps the compiler from moving accesses across it.
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 struct TinyArgs {
     const WorkItem *items;
     int32_t n_items;

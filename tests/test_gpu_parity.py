@@ -1062,6 +1062,57 @@ def test_constant_diagonals(kind, offsets, n, P, schedule):
 
 
 @pytest.mark.parametrize("kind", ["jacobi", "power"])
+@pytest.mark.parametrize("sizes,P", [((255,), 1), ((1,), 1), ((40001,), 7), ((10000,), 900),
+                                     ((129, 255), 3), ((64, 64), 1), ((33, 31), 40),
+                                     ((24, 23, 40), 5), ((30, 30, 30), 200), ((12, 9, 256), 2)])
+def test_queue_of_constant_diagonals(kind, sizes, P):
+    """The pipelined queue sweep over constant diagonals: whole waves (columns
+    of a diagonal in one rank) and mixed ones, ranks from a few rows to one
+    block of all, one item, fewer items than a ticket holds or than a range,
+    and last items of every length; the oracle's iterates and, bit for bit,
+    the general form's iterate, assembled vector and norms, twice."""
+    E = _capi()
+    announce("constant queue", kind, sizes, P)
+    n, T, S = int(np.prod(sizes)), 14, 2
+    strides = [int(np.prod(sizes[:d])) for d in range(len(sizes))]
+    offs = [-s for s in reversed(strides)] + [0] + strides
+    rows = np.arange(n)
+    held = np.ones((n, len(offs)), dtype=bool)
+    for d, (size, stride) in enumerate(zip(sizes, strides)):
+        at = rows // stride % size
+        held[:, len(sizes) - 1 - d] = at > 0
+        held[:, len(sizes) + 1 + d] = at < size - 1
+    v = np.full(len(offs), -1.0) if kind == "jacobi" else np.full(len(offs), 0.9 / len(offs))
+    if kind == "jacobi":
+        v[len(sizes)] = 4.0 * len(sizes)
+    rp = np.zeros(n + 1, dtype=np.int32)
+    rp[1:] = np.cumsum(held.sum(1))
+    A = W.CSR(n, n, rp, (rows[:, None] + np.array(offs))[held].astype(np.int32),
+              np.broadcast_to(v, held.shape)[held].copy())
+    rng = np.random.default_rng(n + P)
+    counts = W.dirichlet_partition(n, P, n) if P > 1 else np.array([n])
+    mask = (rng.random((T, P)) < 0.6).astype(np.uint8)
+    mask[0] = 1
+    prob = W.Iterative("constant-" + kind, kind, A, counts, W.exclusive_scan(counts), S, mask, T,
+                       rng.random(n), **({"b": rng.standard_normal(n), "norm": 2}
+                                         if kind == "jacobi" else
+                                         {"alpha": 0.85, "beta": 0.15 / n, "norm": 1}))
+    kw = {"schedule": E.ECC_SCHEDULE_QUEUE}
+    _solve_and_compare(prob, bitwise=True, solves=2, expect_schedule=E.ECC_SCHEDULE_QUEUE, **kw)
+    outs = []
+    for compact in (E.ECC_COMPACT_AUTO, E.ECC_COMPACT_NONE):
+        run = _iterative(prob, compact=compact, **kw)
+        run.solve(histories=True)
+        torch.cuda.synchronize()
+        outs.append((run.d_x.cpu().numpy(), run.d_x_hat.cpu().numpy(),
+                     run.d_rho.cpu().numpy()[:T]))
+        run.close()
+    for x, y in zip(*outs):
+        assert np.array_equal(x, y)
+    _step_api_matches_solve((prob,), schedule=E.ECC_SCHEDULE_QUEUE)
+
+
+@pytest.mark.parametrize("kind", ["jacobi", "power"])
 @pytest.mark.parametrize("counts", [[20000], [0, 3000, 0, 9000, 1000, 7000], 9])
 def test_solve_sorted_layout(kind, counts):
     """Very uneven rows: each rank's rows are swept in order of decreasing
