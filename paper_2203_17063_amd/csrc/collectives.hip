@@ -98,7 +98,8 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble(
 // the stores out of the chain: the grid's first workgroups only sum (eff
 // ranks are read from fresh, which the slots will equal), further workgroups
 // copy fresh to slot, 4 vectors per thread, and no workgroup reads what
-// another writes.
+// another writes.  HELD: fresh and slots are the same array, so nothing is
+// copied.
 struct ReduceArgs {
     int32_t P, S;
     int64_t t;
@@ -120,7 +121,7 @@ struct ReduceArgs {
 constexpr int kReduceCopies = 4;   // SPLIT: vectors one thread of a copying workgroup moves
 constexpr int kReduceStage = 256;  // ranks staged in LDS at a time
 
-template <int NTH, int W, int VP, int U, bool SPLIT>
+template <int NTH, int W, int VP, int U, bool SPLIT, bool HELD = false>
 __global__ __launch_bounds__(NTH) void k_allreduce(ReduceArgs a) {
     using T = typename WordVec<W>::t;
     __shared__ uint64_t s_src[kReduceStage], s_dst[kReduceStage];
@@ -174,7 +175,7 @@ __global__ __launch_bounds__(NTH) void k_allreduce(ReduceArgs a) {
             const double *f = a.fresh[p];
             double *s = a.slots[p];
             s_src[k] = (uint64_t)(e ? f : s);
-            s_dst[k] = (!SPLIT && e && f != s) ? (uint64_t)s : 0;
+            s_dst[k] = (!SPLIT && !HELD && e && f != s) ? (uint64_t)s : 0;
         }
         __syncthreads();
         // one batch of up to U ranks: every load, then the stores and the sums
@@ -185,24 +186,26 @@ __global__ __launch_bounds__(NTH) void k_allreduce(ReduceArgs a) {
             for (int u = 0; u < U; ++u) {
                 const int32_t k = whole ? k0 + u : min(k0 + u, nc - 1);
                 src[u] = s_src[k];
-                if constexpr (!SPLIT) dst[u] = s_dst[k];
+                if constexpr (!SPLIT && !HELD) dst[u] = s_dst[k];
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 src[u] = wave_uniform(src[u]);
-                if constexpr (!SPLIT) dst[u] = wave_uniform(dst[u]);
+                if constexpr (!SPLIT && !HELD) dst[u] = wave_uniform(dst[u]);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (whole || k0 + u < nc) {
 #pragma unroll
                     for (int j = 0; j < VP; ++j)
-                        v[u][j] = *(GlobalPtr<const T>)((const double *)src[u] + at[j]);
+                        v[u][j] = HELD ? __builtin_nontemporal_load(
+                                             (GlobalPtr<const T>)((const double *)src[u] + at[j]))
+                                       : *(GlobalPtr<const T>)((const double *)src[u] + at[j]);
                 }
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (whole || k0 + u < nc) {
-                    if constexpr (!SPLIT) {
+                    if constexpr (!SPLIT && !HELD) {
                         if (dst[u]) {
 #pragma unroll
                             for (int j = 0; j < VP; ++j)
@@ -294,14 +297,19 @@ __global__ __launch_bounds__(kWideThreads) void k_allreduce_wide(
 //   2 x 8,000,001    41 at 256 x 2 pairs x 4 ranks, 45 at 128 x 1, 44 before
 //   24 x 30,011     4.5 split (the launch itself), 6.1 at 128 x 1, 74 before
 //   64 x 100,001     22 split, 20 at 128 x 1; 256 x 30,011: 22 and 38
+//   32 x 3.5M, fresh and slots the same array (HELD: every contribution is
+//     read once and none copied, so the loads are non-temporal): 27 us less at
+//     256 x 1 pair x 8 ranks than wide (192); 16 x 1.9M: 4 us less than at
+//     256 x 8 x 2; below 16 ranks no difference
 //   256 x 100        9 split at 64 x 1 element x 32 ranks, 12 at 128 x 1 pair
 constexpr int64_t kReduceFill = 200;        // workgroups that fill the 256 CUs well enough
 constexpr int32_t kReduceManyRanks = 16;    // wide chunks pay from here on
 constexpr int64_t kReduceSplitMax = 65536;  // elements: the split form up to here
 constexpr int64_t kReduceTinyMax = 4096;    // elements: single elements, 32 ranks in flight
 constexpr int32_t kReduceSplitRanks = 1024;
+constexpr int64_t kReduceHeldMax = int64_t(1) << 32;  // elements: a launch's 2^31 threads
 
-template <int NTH, int W, int VP, int U, bool SPLIT>
+template <int NTH, int W, int VP, int U, bool SPLIT, bool HELD = false>
 static ecc_status_t launch_reduce(ReduceArgs &a, hipStream_t stream) {
     constexpr int64_t chunk = (int64_t)NTH * W * VP;
     constexpr int64_t copy = (int64_t)NTH * W * kReduceCopies;
@@ -311,7 +319,7 @@ static ecc_status_t launch_reduce(ReduceArgs &a, hipStream_t stream) {
         set_error("m too large");
         return ECC_ERR_RANGE;
     }
-    hipLaunchKernelGGL((k_allreduce<NTH, W, VP, U, SPLIT>), dim3((unsigned)grid), dim3(NTH), 0,
+    hipLaunchKernelGGL((k_allreduce<NTH, W, VP, U, SPLIT, HELD>), dim3((unsigned)grid), dim3(NTH), 0,
                        stream, a);
     ECC_LAUNCH_CHECK();
     return ECC_OK;
@@ -324,6 +332,8 @@ static ecc_status_t launch_reduce_any(ReduceArgs &a, hipStream_t stream) {
         return launch_reduce<128, 2, 1, 16, true>(a, stream);
     }
     if (a.P >= kReduceManyRanks) {
+        if (a.fresh == (const double *const *)a.slots && m < kReduceHeldMax)
+            return launch_reduce<256, 2, 1, 8, false, true>(a, stream);
         constexpr int64_t wide = 2 * kWidePairs * kWideThreads;
         const int64_t grid = 1 + (m + wide - 1) / wide;
         if (grid > 0x7fffffff) {

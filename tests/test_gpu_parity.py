@@ -255,6 +255,42 @@ def test_allreduce_in_place(P, m, S, aligned):
     plan.close()
 
 
+@pytest.mark.parametrize("P,m", [(16, 65537), (17, 65538), (33, 66049), (300, 70001),
+                                 (15, 70001), (40, 600)])
+def test_allreduce_partial_held(P, m):
+    """One array of addresses for contributions and slots: the sum of the
+    slots in rank order, the slots untouched, whatever arrives."""
+    E, R = _capi(), _runner()
+    announce("allreduce held", P, m)
+    rng = np.random.default_rng(P + m)
+    host = rng.standard_normal((P, m))
+    store = torch.zeros((P, m + 2), dtype=torch.float64, device="cuda")
+    held = [store[p, p % 2:p % 2 + m] for p in range(P)]
+    for p in range(P):
+        held[p].copy_(torch.from_numpy(host[p]))
+    before = store.clone()
+    ptrs = R.ptr_array(held)
+    plan = R.Plan(P, None, None, 1)
+    version = np.full(P, -1, dtype=np.int32)
+    ref = host[0].copy()
+    for p in range(1, P):
+        ref = ref + host[p]
+    for r in range(3):
+        mask = (rng.random(P) < 0.5).astype(np.uint8)
+        eff, _, _ = oracle.select(1, r, mask, version)
+        out = torch.full((m,), np.nan, dtype=torch.float64, device="cuda")
+        eff_d = torch.empty(P, dtype=torch.uint8, device="cuda")
+        clk_d = torch.empty(1, dtype=torch.int32, device="cuda")
+        E.ecc_allreduce_partial(plan.handle, m, ptrs, ptrs, out, torch.from_numpy(mask).cuda(),
+                                eff_d, clk_d)
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy(), ref)
+        assert np.array_equal(eff_d.cpu().numpy(), eff)
+        assert int(clk_d.item()) == oracle.result_clock(version)
+        assert torch.equal(store, before)
+    plan.close()
+
+
 @pytest.mark.parametrize("P,m", [
     # (the split form up to 65,536 elements and 1,024 ranks, single elements
     # up to 4,096; then chunks by length, wide ones from 16 ranks on)
