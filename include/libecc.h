@@ -201,6 +201,13 @@ ecc_status_t ecc_allreduce_partial(ecc_plan_t plan, int64_t m, const double *con
                                    const uint8_t *d_arrived, uint8_t *d_eff_out,
                                    int32_t *d_result_clock);
 
+/* Launch shape ecc_allreduce_partial takes for P ranks of m elements (host
+ * only): *workgroups of *threads threads, each access moving *width elements
+ * (at most m of them, for m > 0).  held != 0: d_fresh and d_slots are the same
+ * device array.  ECC_ERR_ARG for P < 1, m < 0 or a NULL output. */
+ecc_status_t ecc_allreduce_shape(int32_t P, int64_t m, int32_t held, int64_t *workgroups,
+                                 int32_t *threads, int32_t *width);
+
 /* ---------------------------------------------------------------------------
  * Block-row iterations consuming the assembled vector.  Rank p owns rows
  * [displs[p], displs[p] + counts[p]); the plan's blocks must tile

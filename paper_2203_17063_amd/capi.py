@@ -70,6 +70,7 @@ _SIGS = [
     ("ecc_plan_timing", ctypes.c_int, [_VP, _I32, _VP, _VP, _I32]),
     ("ecc_allgatherv_assemble", ctypes.c_int, [_VP, _VP, _VP, _VP, _VP, _VP]),
     ("ecc_allgatherv_assemble_packed", ctypes.c_int, [_VP, _VP, _VP, _VP, _VP, _VP]),
+    ("ecc_allreduce_shape", ctypes.c_int, [_I32, _I64, _I32, _VP, _VP, _VP]),
     ("ecc_allreduce_partial", ctypes.c_int, [_VP, _I64, _VP, _VP, _VP, _VP, _VP, _VP]),
     ("ecc_matrix_create", ctypes.c_int, [_VP, ctypes.POINTER(ecc_csr_t), _I32, ctypes.POINTER(_VP)]),
     ("ecc_matrix_create_ex", ctypes.c_int, [_VP, ctypes.POINTER(ecc_csr_t), _I32,
@@ -219,6 +220,14 @@ def ecc_allgatherv_assemble_packed(plan, d_send_base, d_recv, d_arrived, d_eff_o
     _check(lib().ecc_allgatherv_assemble_packed(plan, _ptr(d_send_base), _ptr(d_recv),
                                                 _ptr(d_arrived), _ptr(d_eff_out),
                                                 _ptr(d_age_out)))
+
+
+def ecc_allreduce_shape(P, m, held=False):
+    """(workgroups, threads, elements per access) of the partial allreduce's launch."""
+    groups, threads, width = ctypes.c_int64(0), ctypes.c_int32(0), ctypes.c_int32(0)
+    _check(lib().ecc_allreduce_shape(int(P), int(m), 1 if held else 0, ctypes.byref(groups),
+                                     ctypes.byref(threads), ctypes.byref(width)))
+    return groups.value, threads.value, width.value
 
 
 def ecc_allreduce_partial(plan, m, d_fresh, d_slots, d_result, d_arrived, d_eff_out=None,

@@ -309,52 +309,92 @@ constexpr int64_t kReduceTinyMax = 4096;    // elements: single elements, 32 ran
 constexpr int32_t kReduceSplitRanks = 1024;
 constexpr int64_t kReduceHeldMax = int64_t(1) << 32;  // elements: a launch's 2^31 threads
 
-template <int NTH, int W, int VP, int U, bool SPLIT, bool HELD = false>
-static ecc_status_t launch_reduce(ReduceArgs &a, hipStream_t stream) {
-    constexpr int64_t chunk = (int64_t)NTH * W * VP;
-    constexpr int64_t copy = (int64_t)NTH * W * kReduceCopies;
-    a.n_sum = (a.m + chunk - 1) / chunk;
-    const int64_t grid = 1 + a.n_sum + (SPLIT ? a.P * ((a.m + copy - 1) / copy) : 0);
-    if (grid > 0x7fffffff) {
-        set_error("m too large");
-        return ECC_ERR_RANGE;
+// The shapes a launch can take; kReduceShapes is indexed by them.
+enum ReduceForm {
+    kReduceSplitOne,   // split, single elements
+    kReduceSplitPair,  // split, pairs
+    kReduceOne,        // single elements: vectors shorter than a pair
+    kReducePair,
+    kReduceFew,        // long vectors of few ranks
+    kReduceMiddle,
+    kReduceLonger,
+    kReduceWide,       // k_allreduce_wide
+    kReduceHeld,
+    kReduceForms
+};
+struct ReduceShape {
+    int32_t threads, width, vecs;  // elements per access, accesses per thread and rank
+    bool split;
+};
+constexpr ReduceShape kReduceShapes[kReduceForms] = {
+    {64, 1, 1, true},  {128, 2, 1, true},  {64, 1, 1, false},
+    {128, 2, 1, false}, {256, 2, 2, false}, {256, 2, 8, false},
+    {512, 2, 8, false}, {kWideThreads, 2, kWidePairs, false}, {256, 2, 1, false}};
+
+// held: fresh and slots are one array.  A vector shorter than a pair takes a
+// shape of single elements whatever its ranks: the lanes of a wider one would
+// read and write the element before it.
+static ReduceForm reduce_form(int32_t P, int64_t m, bool held) {
+    if (m <= kReduceSplitMax && P <= kReduceSplitRanks)
+        return m <= kReduceTinyMax ? kReduceSplitOne : kReduceSplitPair;
+    if (m < 2) return kReduceOne;
+    if (P >= kReduceManyRanks) {
+        if (held && m < kReduceHeldMax) return kReduceHeld;
+        if (m >= kReduceFill * 2 * kWidePairs * kWideThreads) return kReduceWide;
+        if (m >= kReduceFill * 8192) return kReduceLonger;
+        if (m >= kReduceFill * 4096) return kReduceMiddle;
+    } else if (m >= (1 << 19)) {
+        return kReduceFew;
     }
-    hipLaunchKernelGGL((k_allreduce<NTH, W, VP, U, SPLIT, HELD>), dim3((unsigned)grid), dim3(NTH), 0,
-                       stream, a);
-    ECC_LAUNCH_CHECK();
-    return ECC_OK;
+    return kReducePair;
 }
 
-static ecc_status_t launch_reduce_any(ReduceArgs &a, hipStream_t stream) {
-    const int64_t m = a.m;
-    if (m <= kReduceSplitMax && a.P <= kReduceSplitRanks) {
-        if (m <= kReduceTinyMax) return launch_reduce<64, 1, 1, 32, true>(a, stream);
-        return launch_reduce<128, 2, 1, 16, true>(a, stream);
+// Workgroups of a launch: one that records, those that sum and, split, those
+// that copy.
+static int64_t reduce_sums(ReduceForm f, int64_t m) {
+    const ReduceShape &s = kReduceShapes[f];
+    const int64_t chunk = (int64_t)s.threads * s.width * s.vecs;
+    return m / chunk + (m % chunk != 0);
+}
+static int64_t reduce_grid(ReduceForm f, int32_t P, int64_t m) {
+    const ReduceShape &s = kReduceShapes[f];
+    const int64_t copy = (int64_t)s.threads * s.width * kReduceCopies;
+    return 1 + reduce_sums(f, m) + (s.split ? P * ((m + copy - 1) / copy) : 0);
+}
+
+template <ReduceForm F, int U, bool HELD = false>
+static void launch_reduce(const ReduceArgs &a, unsigned grid, hipStream_t stream) {
+    constexpr ReduceShape s = kReduceShapes[F];
+    hipLaunchKernelGGL((k_allreduce<s.threads, s.width, s.vecs, U, s.split, HELD>), dim3(grid),
+                       dim3(s.threads), 0, stream, a);
+}
+
+static ecc_status_t launch_reduce_any(ReduceForm f, ReduceArgs &a, hipStream_t stream) {
+    // every lane's access lies in [0, m): at = min(e, m - width) in the kernels
+    if (a.m > 0 && a.m < kReduceShapes[f].width) {
+        set_error("allreduce: %lld elements in accesses of %d", (long long)a.m,
+                  kReduceShapes[f].width);
+        return ECC_ERR_STATE;
     }
-    if (a.P >= kReduceManyRanks) {
-        if (a.fresh == (const double *const *)a.slots && m < kReduceHeldMax)
-            return launch_reduce<256, 2, 1, 8, false, true>(a, stream);
-        constexpr int64_t wide = 2 * kWidePairs * kWideThreads;
-        const int64_t grid = 1 + (m + wide - 1) / wide;
-        if (grid > 0x7fffffff) {
-            set_error("m too large");
-            return ECC_ERR_RANGE;
-        }
-        if (m >= kReduceFill * wide) {
-            hipLaunchKernelGGL(k_allreduce_wide, dim3((unsigned)grid), dim3(kWideThreads), 0,
-                               stream, a.P, a.S, a.t, a.arrived, a.ver_in, a.ver_out, a.age_state,
-                               a.eff_state, a.forced, a.eff_user, a.result_clock, m, a.fresh,
-                               a.slots, a.result);
-            ECC_LAUNCH_CHECK();
-            return ECC_OK;
-        }
-        if (m >= kReduceFill * 8192) return launch_reduce<512, 2, 8, 1, false>(a, stream);
-        if (m >= kReduceFill * 4096) return launch_reduce<256, 2, 8, 2, false>(a, stream);
-    } else if (m >= (1 << 19)) {
-        return launch_reduce<256, 2, 2, 4, false>(a, stream);
+    const unsigned grid = (unsigned)reduce_grid(f, a.P, a.m);
+    a.n_sum = reduce_sums(f, a.m);
+    switch (f) {
+        case kReduceSplitOne: launch_reduce<kReduceSplitOne, 32>(a, grid, stream); break;
+        case kReduceSplitPair: launch_reduce<kReduceSplitPair, 16>(a, grid, stream); break;
+        case kReduceOne: launch_reduce<kReduceOne, 8>(a, grid, stream); break;
+        case kReducePair: launch_reduce<kReducePair, 8>(a, grid, stream); break;
+        case kReduceFew: launch_reduce<kReduceFew, 4>(a, grid, stream); break;
+        case kReduceMiddle: launch_reduce<kReduceMiddle, 2>(a, grid, stream); break;
+        case kReduceLonger: launch_reduce<kReduceLonger, 1>(a, grid, stream); break;
+        case kReduceHeld: launch_reduce<kReduceHeld, 8, true>(a, grid, stream); break;
+        default:
+            hipLaunchKernelGGL(k_allreduce_wide, dim3(grid), dim3(kWideThreads), 0, stream, a.P,
+                               a.S, a.t, a.arrived, a.ver_in, a.ver_out, a.age_state, a.eff_state,
+                               a.forced, a.eff_user, a.result_clock, a.m, a.fresh, a.slots,
+                               a.result);
     }
-    if (m < 2) return launch_reduce<64, 1, 1, 8, false>(a, stream);
-    return launch_reduce<128, 2, 1, 8, false>(a, stream);
+    ECC_LAUNCH_CHECK();
+    return ECC_OK;
 }
 
 ecc_status_t launch_assemble(ecc_plan_t plan, const double *const *d_send,
@@ -420,6 +460,18 @@ ecc_status_t ecc_allgatherv_assemble_packed(ecc_plan_t plan, const double *d_sen
                            nullptr);
 }
 
+ecc_status_t ecc_allreduce_shape(int32_t P, int64_t m, int32_t held, int64_t *workgroups,
+                                 int32_t *threads, int32_t *width) {
+    clear_error();
+    ECC_ARG(P >= 1 && m >= 0, "P must be >= 1 and m >= 0");
+    ECC_ARG(workgroups && threads && width, "NULL output");
+    const ReduceForm f = reduce_form(P, m, held != 0);
+    *workgroups = reduce_grid(f, P, m);
+    *threads = kReduceShapes[f].threads;
+    *width = kReduceShapes[f].width;
+    return ECC_OK;
+}
+
 ecc_status_t ecc_allreduce_partial(ecc_plan_t plan, int64_t m, const double *const *d_fresh,
                                    double *const *d_slots, double *d_result,
                                    const uint8_t *d_arrived, uint8_t *d_eff_out,
@@ -448,9 +500,14 @@ ecc_status_t ecc_allreduce_partial(ecc_plan_t plan, int64_t m, const double *con
     a.fresh = d_fresh;
     a.slots = d_slots;
     a.result = d_result;
+    const ReduceForm form = reduce_form(a.P, m, d_fresh == (const double *const *)d_slots);
+    if (reduce_grid(form, a.P, m) > 0x7fffffff) {
+        set_error("m too large");
+        return ECC_ERR_RANGE;
+    }
     {
         TimedLaunch timed(plan, ECC_TIMING_ALLREDUCE);
-        st = launch_reduce_any(a, plan->stream);
+        st = launch_reduce_any(form, a, plan->stream);
     }
     if (st != ECC_OK) return st;
     plan->clock = t + 1;

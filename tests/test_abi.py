@@ -116,3 +116,20 @@ def test_hypercube_create_checks_without_device(P, m, slack, expect):
     with pytest.raises(E.EccError) as err:
         E.ecc_hypercube_create(P, m, slack)
     assert err.value.status == expect
+
+
+def test_allreduce_shapes():
+    """The partial allreduce's launch over ranks, lengths and whether the
+    contributions are held in their slots: no access is wider than the vector,
+    and the summing threads cover it."""
+    lengths = {0, 1, 2, 3, 600}
+    for e in (4096, 65536, 1 << 19, 200 * 4096, 200 * 8192, 200 * 16384, 1 << 32):
+        lengths |= {e - 1, e, e + 1}
+    for P in (1, 2, 15, 16, 17, 256, 1024, 1025, 5000, (1 << 24) - 1):
+        for m in sorted(lengths):
+            for held in (False, True):
+                groups, threads, width = E.ecc_allreduce_shape(P, m, held)
+                assert threads % 64 == 0 and width in (1, 2) and groups >= 1
+                assert m == 0 or width <= m, (P, m, held)
+                assert m == 0 or groups >= 2, (P, m, held)
+    assert E.lib().ecc_allreduce_shape(0, 1, 0, None, None, None) == E.ECC_ERR_ARG

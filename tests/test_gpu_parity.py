@@ -291,6 +291,35 @@ def test_allreduce_partial_held(P, m):
     plan.close()
 
 
+@pytest.mark.parametrize("m", [1, 2, 3])
+def test_allreduce_partial_held_short(m):
+    """Contributions held in the slots of more ranks than the split form
+    takes, vectors around one pair of elements: the sum in rank order, and
+    nothing written beside the result or to a slot."""
+    E, R = _capi(), _runner()
+    P = 1025
+    announce("allreduce held short", P, m)
+    host = np.random.default_rng(m).standard_normal((P, m))
+    store = torch.full((P, m + 4), 7.0, dtype=torch.float64, device="cuda")
+    store[:, 2:2 + m] = torch.from_numpy(host)
+    before = store.clone()
+    ptrs = R.ptr_array([store[p, 2:2 + m] for p in range(P)])
+    out = torch.full((m + 4,), 5.0, dtype=torch.float64, device="cuda")
+    ref = host[0].copy()
+    for p in range(1, P):
+        ref = ref + host[p]
+    plan = R.Plan(P, None, None, 1)
+    for _ in range(2):
+        E.ecc_allreduce_partial(plan.handle, m, ptrs, ptrs, out[2:2 + m],
+                                torch.ones(P, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()
+        assert np.array_equal(got[2:2 + m], ref)
+        assert (got[:2] == 5.0).all() and (got[2 + m:] == 5.0).all()
+        assert torch.equal(store, before)
+    plan.close()
+
+
 @pytest.mark.parametrize("P,m", [
     # (the split form up to 65,536 elements and 1,024 ranks, single elements
     # up to 4,096; then chunks by length, wide ones from 16 ranks on)
