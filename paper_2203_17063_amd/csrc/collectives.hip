@@ -307,7 +307,9 @@ constexpr int32_t kReduceManyRanks = 16;    // wide chunks pay from here on
 constexpr int64_t kReduceSplitMax = 65536;  // elements: the split form up to here
 constexpr int64_t kReduceTinyMax = 4096;    // elements: single elements, 32 ranks in flight
 constexpr int32_t kReduceSplitRanks = 1024;
-constexpr int64_t kReduceHeldMax = int64_t(1) << 32;  // elements: a launch's 2^31 threads
+// A launch holds fewer than 2^32 threads; from here on 16 elements each.
+constexpr int64_t kReduceHeldMax = int64_t(1) << 32;
+constexpr int64_t kReduceFewMax = int64_t(1) << 33;
 
 // The shapes a launch can take; kReduceShapes is indexed by them.
 enum ReduceForm {
@@ -344,7 +346,7 @@ static ReduceForm reduce_form(int32_t P, int64_t m, bool held) {
         if (m >= kReduceFill * 8192) return kReduceLonger;
         if (m >= kReduceFill * 4096) return kReduceMiddle;
     } else if (m >= (1 << 19)) {
-        return kReduceFew;
+        return m < kReduceFewMax ? kReduceFew : kReduceWide;
     }
     return kReducePair;
 }

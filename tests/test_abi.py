@@ -133,3 +133,14 @@ def test_allreduce_shapes():
                 assert m == 0 or width <= m, (P, m, held)
                 assert m == 0 or groups >= 2, (P, m, held)
     assert E.lib().ecc_allreduce_shape(0, 1, 0, None, None, None) == E.ECC_ERR_ARG
+
+
+@pytest.mark.parametrize("held", [False, True])
+@pytest.mark.parametrize("P", [1, 2, 15, 16, 17, 1024, 1025])
+def test_allreduce_longest_vectors(P, held):
+    """A launch holds fewer than 2^32 threads: vectors of up to nearly 2^36
+    elements (one element per 16 in a thread) fit one whatever the ranks."""
+    for m in (1 << 31, (1 << 32) - 1, 1 << 32, (1 << 33) - 1, 1 << 33, (1 << 33) + 1, 1 << 34,
+              (1 << 35) + 3, (1 << 36) - (1 << 15)):
+        groups, threads, _ = E.ecc_allreduce_shape(P, m, held)
+        assert groups * threads < 1 << 32, (P, m, held)
