@@ -42,7 +42,8 @@ __global__ __launch_bounds__(kThrThreads) void k_bcast_prefix(int32_t P, int32_t
                                                               const double *__restrict__ src,
                                                               double *const *__restrict__ dst) {
     using T = typename WordVec<2>::t;
-    const int32_t p0 = (int32_t)blockIdx.y * per, p1 = min(P, p0 + per);
+    const int32_t p0 = (int32_t)blockIdx.y * per;
+    const int32_t p1 = (int32_t)min((int64_t)P, (int64_t)p0 + per);
     if (k == 1) {
         if (threadIdx.x == 0)
             for (int32_t p = p0; p < p1; ++p)
@@ -223,17 +224,17 @@ __global__ __launch_bounds__(kThrThreads) void k_allreduce_drop(int32_t P, int64
     const int64_t at = max<int64_t>(0, min(e, m - 1));
     double acc = 0.0;
     int32_t total = 0;
-    for (int32_t c0 = 0; c0 < P; c0 += kDropStage) {
+    for (int64_t c0 = 0; c0 < P; c0 += kDropStage) {
         if (c0) __syncthreads();
         // the 64-rank groups of this stage, one wave at a time each
         for (int32_t g = tid >> 6; g < kDropStage / 64; g += kThrThreads / 64) {
-            const int32_t p = c0 + g * 64 + (tid & 63);
+            const int64_t p = c0 + g * 64 + (tid & 63);
             const uint64_t on = __ballot(p < P && arrived[p] != 0);
             if ((tid & 63) == 0) s_wave[g] = __popcll(on);
         }
         __syncthreads();
         for (int32_t g = tid >> 6; g < kDropStage / 64; g += kThrThreads / 64) {
-            const int32_t p = c0 + g * 64 + (tid & 63);
+            const int64_t p = c0 + g * 64 + (tid & 63);
             const bool here = p < P && arrived[p] != 0;
             const uint64_t on = __ballot(here);
             int32_t at0 = 0;
