@@ -230,9 +230,9 @@ __global__ __launch_bounds__(NTH) void k_allreduce(ReduceArgs a) {
 // elements (8 pairs per thread), and one rank's loads are in flight at a
 // time, its addresses and decision read per rank.  At this size the memory
 // sets the pace, and it runs best when all workgroups stream the same rank's
-// vector together: staging the addresses in LDS (2,837 against 2,806 us, 256
-// x 4M), two ranks in flight, or loading the next rank before this one's sums
-// (2,832) were slower, as were all narrower chunks (2,860 to 3,240).
+// vector together.  256 x 4M, on one box (the table below is another's):
+// 2,806 us; 2,837 with the addresses staged in LDS, 2,832 with the next rank
+// loaded before this one's sums, 2,860 to 3,240 in narrower chunks.
 constexpr int kWideThreads = 1024;
 constexpr int kWidePairs = 8;
 
@@ -285,24 +285,32 @@ __global__ __launch_bounds__(kWideThreads) void k_allreduce_wide(
 
 // The shape of the launch by the vectors' length.  Wide chunks (8 pairs per
 // thread, few ranks in flight) stream each rank's vector in long runs, and pay
-// once every CU has a workgroup (kReduceFill of them) and the ranks are many;
-// shorter vectors take chunks of one pair per thread with more ranks in
-// flight instead, and the shortest the split form.  Measured on MI355X, us per
-// call (a 1,024-thread workgroup of 16,384 elements, one rank in flight, for
-// every length before):
-//   256 x 4M      2,623 wide (1,024 x 8 pairs), 2,878 at 128 x 1 pair
-//   256 x 2M      1,329 at 512 x 8, 1,442 at 1,024 x 8, 1,532 at 128 x 1
-//   256 x 1M        659 at 256 x 8, 1,264 at 1,024 x 8, 778 at 128 x 1
-//   64 x 300,001     51 at 128 x 1, 125 at 256 x 8, 301 before; split 74
-//   2 x 8,000,001    41 at 256 x 2 pairs x 4 ranks, 45 at 128 x 1, 44 before
-//   24 x 30,011     4.5 split (the launch itself), 6.1 at 128 x 1, 74 before
-//   64 x 100,001     22 split, 20 at 128 x 1; 256 x 30,011: 22 and 38
+// from 16 ranks on as long as the device holds all of their workgroups at
+// once, one per CU: from kReduceFill of them to kReduceCus for the first, to
+// kReduceCus for the second, and the largest beyond (an 8,192-element chunk
+// of 2.5M makes 306, and the 50 second ones cost a fifth).  Shorter vectors
+// take chunks of one pair per thread with more ranks in flight instead, and
+// the shortest the split form.  Measured on MI355X, us per call, 70 % of the
+// ranks arriving unless stated; "before" is a 1,024-thread workgroup of
+// 16,384 elements, one rank in flight, at every length:
+//                  pairs  4,096  8,192  wide   before
+//   256 x 4,194,304 2,920  2,878  2,822  2,669  2,709
+//   256 x 2,500,000 1,756  1,811  2,077  1,717  1,765
+//   256 x 1,700,001 1,455  1,255  1,087  1,647  2,149
+//   256 x 1,200,000   849    999    795  1,324  1,424
+//   256 x   830,000   586    522    699  1,254  1,333
+//    16 x 2,500,000   107    113    132    112    116
+//    16 x 1,200,000    43     54     50     80     84
+//   48 x 150,001     20 pairs, 23 split, 41 at 4,096, 215 before
+//   2 x 8,000,001    44 at 256 x 2 pairs x 4 ranks, 45 pairs, 53 before
+//   24 x 30,011      4.5 split (the launch itself), 109 before
+//   256 x 40,000     31 split or pairs, 660 before
 //   32 x 3.5M, fresh and slots the same array (HELD: every contribution is
 //     read once and none copied, so the loads are non-temporal): 27 us less at
 //     256 x 1 pair x 8 ranks than wide (192); 16 x 1.9M: 4 us less than at
 //     256 x 8 x 2; below 16 ranks no difference
-//   256 x 100        9 split at 64 x 1 element x 32 ranks, 12 at 128 x 1 pair
-constexpr int64_t kReduceFill = 200;        // workgroups that fill the 256 CUs well enough
+constexpr int64_t kReduceCus = 256;
+constexpr int64_t kReduceFill = 200;        // workgroups that fill them well enough
 constexpr int32_t kReduceManyRanks = 16;    // wide chunks pay from here on
 constexpr int64_t kReduceSplitMax = 65536;  // elements: the split form up to here
 constexpr int64_t kReduceTinyMax = 4096;    // elements: single elements, 32 ranks in flight
@@ -333,6 +341,11 @@ constexpr ReduceShape kReduceShapes[kReduceForms] = {
     {128, 2, 1, false}, {256, 2, 2, false}, {256, 2, 8, false},
     {512, 2, 8, false}, {kWideThreads, 2, kWidePairs, false}, {256, 2, 1, false}};
 
+// Elements of each rank's vector a workgroup owns.
+constexpr int64_t reduce_chunk(ReduceForm f) {
+    return (int64_t)kReduceShapes[f].threads * kReduceShapes[f].width * kReduceShapes[f].vecs;
+}
+
 // held: fresh and slots are one array.  A vector shorter than a pair takes a
 // shape of single elements whatever its ranks: the lanes of a wider one would
 // read and write the element before it.
@@ -342,9 +355,9 @@ static ReduceForm reduce_form(int32_t P, int64_t m, bool held) {
     if (m < 2) return kReduceOne;
     if (P >= kReduceManyRanks) {
         if (held && m < kReduceHeldMax) return kReduceHeld;
-        if (m >= kReduceFill * 2 * kWidePairs * kWideThreads) return kReduceWide;
-        if (m >= kReduceFill * 8192) return kReduceLonger;
-        if (m >= kReduceFill * 4096) return kReduceMiddle;
+        if (m > kReduceCus * reduce_chunk(kReduceLonger)) return kReduceWide;
+        if (m > kReduceCus * reduce_chunk(kReduceMiddle)) return kReduceLonger;
+        if (m >= kReduceFill * reduce_chunk(kReduceMiddle)) return kReduceMiddle;
     } else if (m >= (1 << 19)) {
         return m < kReduceFewMax ? kReduceFew : kReduceWide;
     }
@@ -354,8 +367,7 @@ static ReduceForm reduce_form(int32_t P, int64_t m, bool held) {
 // Workgroups of a launch: one that records, those that sum and, split, those
 // that copy.
 static int64_t reduce_sums(ReduceForm f, int64_t m) {
-    const ReduceShape &s = kReduceShapes[f];
-    const int64_t chunk = (int64_t)s.threads * s.width * s.vecs;
+    const int64_t chunk = reduce_chunk(f);
     return m / chunk + (m % chunk != 0);
 }
 static int64_t reduce_grid(ReduceForm f, int32_t P, int64_t m) {

@@ -144,3 +144,13 @@ def test_allreduce_longest_vectors(P, held):
               (1 << 35) + 3, (1 << 36) - (1 << 15)):
         groups, threads, _ = E.ecc_allreduce_shape(P, m, held)
         assert groups * threads < 1 << 32, (P, m, held)
+
+
+def test_allreduce_wide_chunks_run_together():
+    """Chunks of 16 elements per thread below the widest are taken only while
+    the device's 256 CUs hold all of their workgroups, one each."""
+    for P in (16, 48, 256, 2000):
+        for m in range(600001, 5000000, 99991):
+            groups, threads, _ = E.ecc_allreduce_shape(P, m)
+            if threads < 1024 and m > 8 * threads * (groups - 1):
+                assert 100 <= groups - 1 <= 256, (P, m, groups)
