@@ -305,18 +305,24 @@ __global__ __launch_bounds__(kWideThreads) void k_allreduce_wide(
 //   2 x 8,000,001    44 at 256 x 2 pairs x 4 ranks, 45 pairs, 53 before
 //   24 x 30,011      4.5 split (the launch itself), 109 before
 //   256 x 40,000     31 split or pairs, 660 before
-//   32 x 3.5M, fresh and slots the same array (HELD: every contribution is
-//     read once and none copied, so the loads are non-temporal): 27 us less at
-//     256 x 1 pair x 8 ranks than wide (192); 16 x 1.9M: 4 us less than at
-//     256 x 8 x 2; below 16 ranks no difference
+// Where fresh and slots are one array (HELD) a producer has written the slots
+// and none is copied.  Non-temporal loads of one pair per thread, eight ranks
+// in flight, then pay between the size of the Infinity Cache, which holds what
+// was just written, and four times that, where the widest chunk catches up.
+// With a producer that writes four fifths of the slots before each call, us
+// of both: 24 x 3,520,000 (645 MiB) 271 against 303 in the shapes above and
+// 306 before; 32 x 3,520,000 (860 MiB) 359, 387, 390; 64 x 1,700,001 (830
+// MiB) 303, 329, 412; but 64 x 4,194,304 (2 GiB) 911, 863, 868; 128 x
+// 4,194,304 1,783, 1,669, 1,684; 128 x 150,001 (147 MiB) 57, 47, 277.
 constexpr int64_t kReduceCus = 256;
 constexpr int64_t kReduceFill = 200;        // workgroups that fill them well enough
 constexpr int32_t kReduceManyRanks = 16;    // wide chunks pay from here on
 constexpr int64_t kReduceSplitMax = 65536;  // elements: the split form up to here
 constexpr int64_t kReduceTinyMax = 4096;    // elements: single elements, 32 ranks in flight
 constexpr int32_t kReduceSplitRanks = 1024;
+constexpr int64_t kReduceHeldMin = int64_t(1) << 25;  // elements of all ranks: 256 MiB
+constexpr int64_t kReduceHeldMax = int64_t(1) << 27;  // 1 GiB
 // A launch holds fewer than 2^32 threads; from here on 16 elements each.
-constexpr int64_t kReduceHeldMax = int64_t(1) << 32;
 constexpr int64_t kReduceFewMax = int64_t(1) << 33;
 
 // The shapes a launch can take; kReduceShapes is indexed by them.
@@ -354,7 +360,7 @@ static ReduceForm reduce_form(int32_t P, int64_t m, bool held) {
         return m <= kReduceTinyMax ? kReduceSplitOne : kReduceSplitPair;
     if (m < 2) return kReduceOne;
     if (P >= kReduceManyRanks) {
-        if (held && m < kReduceHeldMax) return kReduceHeld;
+        if (held && m > kReduceHeldMin / P && m <= (kReduceHeldMax - 1) / P) return kReduceHeld;
         if (m > kReduceCus * reduce_chunk(kReduceLonger)) return kReduceWide;
         if (m > kReduceCus * reduce_chunk(kReduceMiddle)) return kReduceLonger;
         if (m >= kReduceFill * reduce_chunk(kReduceMiddle)) return kReduceMiddle;

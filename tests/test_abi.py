@@ -154,3 +154,12 @@ def test_allreduce_wide_chunks_run_together():
             groups, threads, _ = E.ecc_allreduce_shape(P, m)
             if threads < 1024 and m > 8 * threads * (groups - 1):
                 assert 100 <= groups - 1 <= 256, (P, m, groups)
+
+
+def test_allreduce_held_range():
+    """Contributions held in their slots have a shape of their own between
+    256 MiB and 1 GiB of them only."""
+    for P in (16, 24, 64, 256, 2000):
+        for m in (70001, 150001, 400000, 1700001, 3520000, 4194304, 8000001):
+            own = E.ecc_allreduce_shape(P, m, True) != E.ecc_allreduce_shape(P, m, False)
+            assert own == (256 << 20 < 8 * P * m < 1 << 30), (P, m)

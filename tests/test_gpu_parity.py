@@ -255,8 +255,10 @@ def test_allreduce_in_place(P, m, S, aligned):
     plan.close()
 
 
+# (the shape of their own begins at 2^25 elements of all ranks)
 @pytest.mark.parametrize("P,m", [(16, 65537), (17, 65538), (33, 66049), (300, 70001),
-                                 (15, 70001), (40, 600)])
+                                 (15, 70001), (40, 600), (16, (1 << 21) + 1), (17, 1973791),
+                                 (300, 111849), (1025, 32737)])
 def test_allreduce_partial_held(P, m):
     """One array of addresses for contributions and slots: the sum of the
     slots in rank order, the slots untouched, whatever arrives."""
