@@ -33,18 +33,30 @@ namespace ecc {
 __device__ __forceinline__ void hc_st(double *p, double v) { __builtin_nontemporal_store(v, p); }
 __device__ __forceinline__ double hc_ld(const double *p) { return __builtin_nontemporal_load(p); }
 
-// Two neighbouring elements of a row by one 16-byte access at any 8-byte
-// alignment; a row's last element alone where m is odd (live = 1).
-typedef WordVec<2>::t HcPair;
-__device__ __forceinline__ HcPair hc_ld2(const double *p, int live) {
-    HcPair v = HcPair(0.0);
-    if (live == 2) v = __builtin_nontemporal_load((GlobalPtr<const HcPair>)p);
-    else if (live == 1) v.x = hc_ld(p);
-    return v;
+// W neighbouring elements of a row by one access at any 8-byte alignment;
+// live of them lie in the row (W = 2: a row's last element alone where m is
+// odd).
+template <int W>
+__device__ __forceinline__ typename WordVec<W>::t hc_ld(const double *p, int live) {
+    typedef typename WordVec<W>::t T;
+    if constexpr (W == 1) {
+        return live ? hc_ld(p) : 0.0;
+    } else {
+        T v = T(0.0);
+        if (live == 2) v = __builtin_nontemporal_load((GlobalPtr<const T>)p);
+        else if (live == 1) v.x = hc_ld(p);
+        return v;
+    }
 }
-__device__ __forceinline__ void hc_st2(double *p, HcPair v, int live) {
-    if (live == 2) __builtin_nontemporal_store(v, (GlobalPtr<HcPair>)p);
-    else if (live == 1) hc_st(p, v.x);
+template <int W>
+__device__ __forceinline__ void hc_st(double *p, typename WordVec<W>::t v, int live) {
+    typedef typename WordVec<W>::t T;
+    if constexpr (W == 1) {
+        if (live) hc_st(p, v);
+    } else {
+        if (live == 2) __builtin_nontemporal_store(v, (GlobalPtr<T>)p);
+        else if (live == 1) hc_st(p, v.x);
+    }
 }
 
 constexpr int kHcThreads = 256;
@@ -157,28 +169,30 @@ __global__ __launch_bounds__(kHcThreads) void k_allreduce_ssp(HcArgs a) {
 }
 
 // Split layout, for 8 to 32 processes and for the 32-process sub-cubes of
-// larger calls: the 2^D partials of a pair of elements are held by the W = 2^LW
-// waves of a workgroup, 2^D / W each (wave w holds processes w 2^D / W + i),
-// so that every decision stays uniform in a wave and a thread holds few
-// partials.  Steps 0 .. D-LW-1 pair processes within a wave; each of the
+// larger calls: the 2^D partials of V neighbouring elements are held by the
+// W = 2^LW waves of a workgroup, 2^D / W each (wave w holds processes
+// w 2^D / W + i), so that every decision stays uniform in a wave and a thread
+// holds few partials.  Steps 0 .. D-LW-1 pair processes within a wave; each of the
 // last LW steps pairs process w 2^D / W + i with the same i of wave
 // w XOR 2^(k-D+LW), whose old partials the waves exchange through LDS.  The
 // additions are those of k_allreduce_ssp, in the same order.  With CUBE,
 // blockIdx.y selects the sub-cube of processes 2^D y .. 2^D (y + 1) - 1,
 // whose fresh flags for steps 0 .. D-1 come from fresh_in, and the partials
-// go to the result for the remaining steps.  Measured on MI355X (32
-// processes x 16 MB, slack 2, 80 % delivery): 735 us per call (5.1 TB/s) with
-// two elements, 16 bytes, per lane (78 VGPRs, four workgroups per CU by LDS;
-// exchanging half of the partials at a time, five, measured the same), 780 us
-// with one.  By waves, at one element per lane: 789 us with four, 885 us with
-// two, 827 us with eight, against 937 us with the 32 partials in one thread.
-template <int D, int LW, bool CUBE>
+// go to the result for the remaining steps.  Pairs (V = 2, 16 bytes per lane:
+// 78 VGPRs, four workgroups per CU by LDS; exchanging half of the partials at
+// a time, five, measured the same) move long rows faster; short rows want the
+// larger grid of single elements (hc_pairs).  By waves, measured on MI355X at
+// V = 1 (32 processes x 16 MB, slack 2, 80 % delivery): 789 us per call with
+// four, 885 us with two, 827 us with eight, against 937 us with the 32
+// partials in one thread.
+template <int D, int LW, bool CUBE, int V>
 __global__ __launch_bounds__(64 << LW) void k_allreduce_ssp_split(HcArgs a,
                                                                   const uint8_t *__restrict__ fresh_in) {
+    typedef typename WordVec<V>::t T;
     constexpr int Pt = 1 << D, W = 1 << LW, H = Pt / W;
     static_assert(LW >= 1 && LW < D && D <= kHcMaxDims, "a split of at most 32 processes");
     __shared__ unsigned long long s_fresh[kHcMaxDims];
-    __shared__ HcPair s_x[W][H][64];
+    __shared__ T s_x[W][H][64];
     const int32_t pc = CUBE ? (int32_t)blockIdx.y * Pt : 0;  // the sub-cube's first process
     if constexpr (CUBE) {
         if (threadIdx.x < 64) {
@@ -200,14 +214,14 @@ __global__ __launch_bounds__(64 << LW) void k_allreduce_ssp_split(HcArgs a,
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t m = a.m;
     const int64_t sd = CUBE ? (int64_t)a.D : D;  // slots per process
-    const int64_t j = 2 * ((int64_t)blockIdx.x * 64 + lane);
-    const int live = j + 1 < m ? 2 : j < m ? 1 : 0;  // elements of this lane
+    const int64_t j = V * ((int64_t)blockIdx.x * 64 + lane);
+    const int live = j + V <= m ? V : j < m ? 1 : 0;  // elements of this lane
     const int p0 = wv * H;  // this wave's first process in the (sub-)cube
     auto slot = [&](int i, int k) { return a.slots + ((int64_t)(pc + p0 + i) * sd + k) * m + j; };
-    HcPair part[H];
+    T part[H];
 #pragma unroll
     for (int i = 0; i < H; ++i)
-        part[i] = hc_ld2(a.contrib + (int64_t)(pc + p0 + i) * m + j, live);
+        part[i] = hc_ld<V>(a.contrib + (int64_t)(pc + p0 + i) * m + j, live);
 #pragma unroll
     for (int k = 0; k < D - LW; ++k) {
         const int bit = 1 << k;
@@ -217,10 +231,10 @@ __global__ __launch_bounds__(64 << LW) void k_allreduce_ssp_split(HcArgs a,
             const int q = i | bit;
             const bool fr = (fresh[k] >> (p0 + i)) & 1ull, fq = (fresh[k] >> (p0 + q)) & 1ull;
             double *sr = slot(i, k), *sq = slot(q, k);
-            const HcPair gr = fr ? part[q] : hc_ld2(sr, live);
-            const HcPair gq = fq ? part[i] : hc_ld2(sq, live);
-            if (fr) hc_st2(sr, gr, live);
-            if (fq) hc_st2(sq, gq, live);
+            const T gr = fr ? part[q] : hc_ld<V>(sr, live);
+            const T gq = fq ? part[i] : hc_ld<V>(sq, live);
+            if (fr) hc_st<V>(sr, gr, live);
+            if (fq) hc_st<V>(sq, gq, live);
             part[i] = part[i] + gr;
             part[q] = part[q] + gq;
         }
@@ -236,15 +250,15 @@ __global__ __launch_bounds__(64 << LW) void k_allreduce_ssp_split(HcArgs a,
         for (int i = 0; i < H; ++i) {
             const bool fr = (fresh[k] >> (p0 + i)) & 1ull;
             double *sr = slot(i, k);
-            const HcPair gr = fr ? s_x[pw][i][lane] : hc_ld2(sr, live);
-            if (fr) hc_st2(sr, gr, live);
+            const T gr = fr ? s_x[pw][i][lane] : hc_ld<V>(sr, live);
+            if (fr) hc_st<V>(sr, gr, live);
             part[i] = part[i] + gr;
         }
         if (k + 1 < D) __syncthreads();  // every partner read before the next writes
     }
 #pragma unroll
     for (int i = 0; i < H; ++i)
-        hc_st2(a.result + (int64_t)(pc + p0 + i) * m + j, part[i], live);
+        hc_st<V>(a.result + (int64_t)(pc + p0 + i) * m + j, part[i], live);
 }
 
 // More than 32 processes.  One call is then three kinds of launch:
@@ -358,13 +372,33 @@ void hc_launch(dim3 grid, hipStream_t st, const HcArgs &a) {
     hipLaunchKernelGGL((k_allreduce_ssp<D>), grid, dim3(kHcThreads), 0, st, a);
 }
 
-constexpr int kHcSplitLW = 2;  // four waves per 128 elements
+constexpr int kHcSplitLW = 2;  // four waves per workgroup
 
-template <int D>
-void hc_launch_split(int64_t m, hipStream_t st, const HcArgs &a) {
-    const int64_t g = std::max<int64_t>(1, (m + 127) / 128);
-    hipLaunchKernelGGL((k_allreduce_ssp_split<D, kHcSplitLW, false>), dim3((unsigned)g),
-                       dim3(64 << kHcSplitLW), 0, st, a, nullptr);
+// Two elements per lane where their grid, of half the workgroups, still gives
+// every CU three; one where it does not.  Measured on MI355X, us per call with
+// one / two elements (slack 2, 80 % delivery):
+//    8 x 16,001   5.9 /  5.9    8 x 160,000   15.2 /  11.5
+//   32 x 2,000    9.6 / 11.3   32 x 80,000    33.2 /  34.2   32 x 700,001  416 / 339
+//   32 x 28,000  18.9 / 22.0   32 x 100,001   58.7 /  54.3   32 x 2^21     783 / 744
+//   64 x 36,000  49.1 / 50.6   64 x 54,001    81.9 /  79.5   64 x 700,001 1,022 / 869
+//  256 x 4,000   45.2 / 46.7  256 x 16,001   150.3 / 129.0  256 x 220,000 1,327 / 1,300
+constexpr int64_t kHcPairFill = 768;
+bool hc_pairs(int32_t P, int64_t m) {
+    return (m + 127) / 128 * std::max(1, P >> kHcCubeDims) >= kHcPairFill;
+}
+
+template <int D, bool CUBE>
+void hc_launch_split(int32_t P, int64_t m, hipStream_t st, const HcArgs &a,
+                     const uint8_t *fresh) {
+    const bool pairs = hc_pairs(P, m);
+    const int64_t per = pairs ? 128 : 64;
+    const dim3 grid((unsigned)std::max<int64_t>(1, (m + per - 1) / per), CUBE ? P >> D : 1);
+    if (pairs)
+        hipLaunchKernelGGL((k_allreduce_ssp_split<D, kHcSplitLW, CUBE, 2>), grid,
+                           dim3(64 << kHcSplitLW), 0, st, a, fresh);
+    else
+        hipLaunchKernelGGL((k_allreduce_ssp_split<D, kHcSplitLW, CUBE, 1>), grid,
+                           dim3(64 << kHcSplitLW), 0, st, a, fresh);
 }
 
 }  // namespace
@@ -387,8 +421,8 @@ ecc_status_t ecc_hypercube_create(int32_t P, int64_t m, int32_t slack, void *hip
         set_error("P * d * m too large");
         return ECC_ERR_RANGE;
     }
-    // one thread per element and at most 64 elements per workgroup: the
-    // grid's x extent holds at most 2^31 - 1 workgroups
+    // a workgroup takes at least 64 elements, and the grid's x extent holds at
+    // most 2^31 - 1 workgroups
     if (m > (int64_t)0x7fffffff * 64) {
         set_error("m too large");
         return ECC_ERR_RANGE;
@@ -488,10 +522,7 @@ ecc_status_t ecc_allreduce_ssp(ecc_hypercube_t h, const double *d_contrib,
         hipLaunchKernelGGL(k_hc_decide_big, dim3(1), dim3(kHcDecideThreads), 0, h->stream, a,
                            h->d_fresh);
         ECC_LAUNCH_CHECK();
-        const int64_t g = std::max<int64_t>(1, (h->m + 127) / 128);
-        hipLaunchKernelGGL((k_allreduce_ssp_split<kHcCubeDims, kHcSplitLW, true>),
-                           dim3((unsigned)g, h->P >> kHcCubeDims), dim3(64 << kHcSplitLW), 0,
-                           h->stream, a, h->d_fresh);
+        hc_launch_split<kHcCubeDims, true>(h->P, h->m, h->stream, a, h->d_fresh);
         ECC_LAUNCH_CHECK();
         for (int32_t k = kHcCubeDims; k < h->D; ++k) {
             hipLaunchKernelGGL(k_hc_pair_step, dim3(h->grid, h->P / 2), dim3(kHcThreads), 0,
@@ -505,9 +536,9 @@ ecc_status_t ecc_allreduce_ssp(ecc_hypercube_t h, const double *d_contrib,
         case 0: hc_launch<0>(grid, h->stream, a); break;
         case 1: hc_launch<1>(grid, h->stream, a); break;
         case 2: hc_launch<2>(grid, h->stream, a); break;
-        case 3: hc_launch_split<3>(h->m, h->stream, a); break;
-        case 4: hc_launch_split<4>(h->m, h->stream, a); break;
-        default: hc_launch_split<5>(h->m, h->stream, a); break;
+        case 3: hc_launch_split<3, false>(h->P, h->m, h->stream, a, nullptr); break;
+        case 4: hc_launch_split<4, false>(h->P, h->m, h->stream, a, nullptr); break;
+        default: hc_launch_split<5, false>(h->P, h->m, h->stream, a, nullptr); break;
     }
     ECC_LAUNCH_CHECK();
     h->clock += 1;

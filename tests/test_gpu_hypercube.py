@@ -82,10 +82,20 @@ def test_parity_ragged_lengths(m):
 @pytest.mark.parametrize("P", [8, 32, 64])
 @pytest.mark.parametrize("m", [2, 63, 127, 128, 129, 255, 257])
 def test_parity_pairs(P, m):
-    """Two elements per lane, 128 per workgroup: lengths around the tile, a
-    last element without a partner, rows at odd multiples of 8 bytes, and
-    every call in place."""
+    """Short rows: lengths around a workgroup's 64 elements, rows at odd
+    multiples of 8 bytes, and every call in place."""
     _run_and_compare(P, m, 1, 0.6, T=5, seed=P + m, in_place=True)
+
+
+@pytest.mark.parametrize("P", [8, 16, 32, 64, 128])
+@pytest.mark.parametrize("past", [0, 1, 2, 65, 127, 128, 129])
+def test_parity_pairs_long_rows(P, past):
+    """Around the length from which a lane carries two elements (768
+    workgroups of 128, over all sub-cubes of 32): the last length of single
+    elements, then a last workgroup of every kind, a last element without a
+    partner, rows at odd multiples of 8 bytes, in place and not."""
+    m = 128 * (768 // max(1, P // 32) - 1) + past
+    _run_and_compare(P, m, 1, 0.6, T=4, seed=P + past, in_place=past % 2 == 1)
 
 
 @pytest.mark.parametrize("P,m,slack,q,in_place", [
