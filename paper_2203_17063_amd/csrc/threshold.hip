@@ -203,9 +203,8 @@ __global__ __launch_bounds__(kThrThreads) void k_reduce_bst_big(
 // a test or a pointer chase between them; each contribution is read once,
 // non-temporally, by one lane per element of a grid without a loop.
 // Measured on MI355X, 26 of 32 ranks x 8.4M: 332 us (5.5 TB/s), against 451
-// us for 2,048 resident workgroups walking the vector with eight ranks' loads
-// behind a test each; pairs per lane 337 to 371 us; 38 of 48 x 30,011: 5.0
-// against 12.7 us.
+// us for k_allreduce_drop_few; pairs per lane 337 to 371 us; 38 of 48 x
+// 30,011: 5.0 against 12.7 us.
 constexpr int kDropStage = 256;
 
 constexpr int kDropU = 16;  // ranks whose loads are in flight together
@@ -277,6 +276,53 @@ __global__ __launch_bounds__(kThrThreads) void k_allreduce_drop(int32_t P, int64
     }
     if (e < m) result[e] = acc;
     if (count && blockIdx.x == 0 && tid == 0) *count = total;
+}
+
+// The same for few ranks, whose list costs a workgroup more than its 256
+// elements' sums: at most kDropFewGrid workgroups walk the vector, a test
+// before each rank's load, eight loads in flight.  Measured on MI355X, us per
+// call alone / in a pass with a Broadcast and a Reduce of the same vectors,
+// with the walk, and with the list: 1 of 2 x 6,000,001 18.0 / 44.5 and 52.9 /
+// 77.2; 3 of 5 x 3M 19.5 / 44.0 and 32.3 / 55.6; 5 of 8 x 3M 26.3 / 63.0 and
+// 36.0 / 70.3, x 8M 92 / 195 and 88 / 180; 6 of 9 x 4,000,001 41 / 116 and 51 /
+// 101; 7 of 10 x 700,001 11.1 / 28.0 and 10.3 / 26.6.
+constexpr int kDropFewU = 8;
+constexpr int64_t kDropFewGrid = 2048;  // eight workgroups per CU
+constexpr int32_t kDropFewRanks = 7;    // the walk at every length
+constexpr int32_t kDropFewRanksHot = 9;               // and up to kDropFewHot
+constexpr int64_t kDropFewHot = int64_t(1) << 25;     // elements of all ranks: 256 MiB
+
+bool drop_few(int32_t P, int64_t m) {
+    return P <= kDropFewRanks || (P <= kDropFewRanksHot && m <= kDropFewHot / P);
+}
+
+__global__ __launch_bounds__(kThrThreads) void k_allreduce_drop_few(
+    int32_t P, int64_t m, const double *const *__restrict__ fresh,
+    const uint8_t *__restrict__ arrived, double *__restrict__ result,
+    int32_t *__restrict__ count) {
+    if (count && blockIdx.x == 0 && threadIdx.x == 0) {
+        int32_t c = 0;
+        for (int32_t p = 0; p < P; ++p) c += arrived[p] != 0;
+        *count = c;
+    }
+    const int64_t stride = (int64_t)gridDim.x * kThrThreads;
+    for (int64_t j = (int64_t)blockIdx.x * kThrThreads + threadIdx.x; j < m; j += stride) {
+        double acc = 0.0;
+        for (int32_t p0 = 0; p0 < P; p0 += kDropFewU) {
+            bool on[kDropFewU];
+            double v[kDropFewU];
+#pragma unroll
+            for (int u = 0; u < kDropFewU; ++u) {
+                const int32_t p = p0 + u;
+                on[u] = p < P && arrived[p] != 0;
+                v[u] = on[u] ? fresh[p][j] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < kDropFewU; ++u)
+                if (on[u]) acc = acc + v[u];
+        }
+        result[j] = acc;
+    }
 }
 
 int64_t thr_prefix(double theta, int64_t m) {
@@ -390,6 +436,13 @@ ecc_status_t ecc_allreduce_drop(int32_t P, int64_t m, const double *const *d_fre
     ECC_ARG(d_arrived != nullptr, "d_arrived is NULL");
     ECC_ARG(m == 0 || (d_fresh && d_result), "NULL contribution array or result");
     if (m == 0 && !d_count) return ECC_OK;
+    if (drop_few(P, m)) {
+        const int64_t grid = std::min(kDropFewGrid, (int64_t)thr_grid_once(m));
+        hipLaunchKernelGGL(k_allreduce_drop_few, dim3((unsigned)grid), dim3(kThrThreads), 0,
+                           (hipStream_t)hip_stream, P, m, d_fresh, d_arrived, d_result, d_count);
+        ECC_LAUNCH_CHECK();
+        return ECC_OK;
+    }
     // (a launch holds fewer than 2^32 threads)
     int64_t e0 = 0;
     do {

@@ -202,23 +202,60 @@ def test_reduce_random(seed):
     assert np.array_equal(res.cpu().numpy(), res_h)
 
 
-def test_allreduce_drop_beyond_one_launch():
-    """A vector of more elements than one launch has threads (2^32): every
-    element is summed, two launches' worth past the first boundary."""
+@pytest.mark.parametrize("P,m", [(1, (1 << 32) + 515), (10, (1 << 31) + 515)])
+def test_allreduce_drop_beyond_one_launch(P, m):
+    """More elements than one launch has threads (few ranks) or takes at once
+    (2^31, the ranks' list; one buffer as every rank's contribution): every
+    element is summed."""
     E = _E()
-    m = (1 << 32) + 515
-    announce("drop, 2^32 elements", m)
+    announce("drop, long vectors", P, m)
     x = torch.empty(m, dtype=torch.float64, device="cuda")
     x.uniform_(-1.0, 1.0)
     res = torch.zeros(m, dtype=torch.float64, device="cuda")
-    arrived = torch.ones(1, dtype=torch.uint8, device="cuda")
+    arrived = torch.ones(P, dtype=torch.uint8, device="cuda")
     cnt = torch.zeros(1, dtype=torch.int32, device="cuda")
-    E.ecc_allreduce_drop(1, m, _ptrs([x]), arrived, res, cnt, _stream())
+    E.ecc_allreduce_drop(P, m, _ptrs([x] * P), arrived, res, cnt, _stream())
     torch.cuda.synchronize()
-    assert int(cnt.item()) == 1
+    assert int(cnt.item()) == P
     step = 1 << 30
     for a in range(0, m, step):
-        assert bool((res[a:a + step] == x[a:a + step]).all()), a
+        ref = x[a:a + step].clone()
+        for _ in range(P - 1):
+            ref += x[a:a + step]
+        assert bool((res[a:a + step] == ref).all()), a
+
+
+@pytest.mark.parametrize("P,m", [(1, 3), (7, 0), (7, 70001), (8, 1 << 20), (9, 3728270),
+                                 (8, (1 << 22) + 1), (9, 3728271), (10, 1), (10, 257),
+                                 (16, 100001), (17, 300)])
+def test_allreduce_drop_ranks(P, m):
+    """The walk of few ranks and the list, at the lengths and rank counts
+    between them: sums in rank order from +0, in place of an arrived rank's
+    contribution too, none arrived, infinities, NaN and signed zeros."""
+    E = _E()
+    announce("drop ranks", P, m)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(P + m)
+    src = torch.rand(P, m, generator=g, dtype=torch.float64, device="cuda") - 0.5
+    src[:, :1] = -0.0
+    if m > 2:
+        src[0, m // 2] = float("nan")
+        src[P - 1, m - 1] = float("-inf")
+    rng = np.random.default_rng(P + m)
+    for arrived_h in (np.zeros(P, np.uint8), (rng.random(P) < 0.7).astype(np.uint8),
+                      np.full(P, 3, np.uint8)):
+        arrived = torch.from_numpy(arrived_h).cuda()
+        ref = torch.zeros(m, dtype=torch.float64, device="cuda")
+        for p in range(P):
+            if arrived_h[p]:
+                ref += src[p]
+        work = src.clone()
+        res = work[P - 1] if arrived_h[P - 1] else torch.empty_like(ref)
+        cnt = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+        E.ecc_allreduce_drop(P, m, _ptrs(list(work)), arrived, res, cnt, _stream())
+        assert int(cnt) == int((arrived_h != 0).sum())
+        same = res.view(torch.int64) == ref.view(torch.int64)
+        assert bool((same | (res.isnan() & ref.isnan())).all())
 
 
 def test_threshold_errors():
