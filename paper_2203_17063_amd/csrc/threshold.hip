@@ -200,8 +200,12 @@ __global__ __launch_bounds__(kThrThreads) void k_reduce_bst_big(
 // that arrived, in rank order.  Read-bound: 8 m (arrived + 1) bytes.  Each
 // workgroup lists the arrived ranks' addresses in LDS (kDropStage ranks at a
 // time, in rank order), so that the loads of U ranks go out together without
-// a test or a pointer chase between them; each contribution is read once,
-// non-temporally, by one lane per element of a grid without a loop.
+// a test or a pointer chase between them; each contribution is read once by
+// one lane per element of a grid without a loop, non-temporally where the
+// contributions of all ranks exceed the Infinity Cache (us per call alone / in
+// a pass with a Broadcast and a Reduce, ordinary and non-temporal loads: 16 x
+// 2M, 244 MiB, 32.6 / 81.1 and 38.6 / 83.7; 12 x 2M 26.4 / 60.4 and 31.6 /
+// 65.9; 16 x 3M, 366 MiB, 50.1 / 136.6 and 55.5 / 120.1).
 // Measured on MI355X, 26 of 32 ranks x 8.4M: 332 us (5.5 TB/s), against 451
 // us for k_allreduce_drop_few; pairs per lane 337 to 371 us; 38 of 48 x
 // 30,011: 5.0 against 12.7 us.
@@ -210,6 +214,13 @@ constexpr int kDropStage = 256;
 constexpr int kDropU = 16;  // ranks whose loads are in flight together
 constexpr int64_t kDropLaunch = int64_t(1) << 31;  // elements of one launch
 
+template <bool NT>
+__device__ __forceinline__ double drop_load(uint64_t src, int64_t at) {
+    const GlobalPtr<const double> p = (GlobalPtr<const double>)((const double *)src + at);
+    return NT ? __builtin_nontemporal_load(p) : *p;
+}
+
+template <bool NT>
 __global__ __launch_bounds__(kThrThreads) void k_allreduce_drop(int32_t P, int64_t e0,
                                                         int64_t m,
                                                         const double *const *__restrict__ fresh,
@@ -255,7 +266,7 @@ __global__ __launch_bounds__(kThrThreads) void k_allreduce_drop(int32_t P, int64
             for (int u = 0; u < kDropU; ++u) src[u] = wave_uniform(s_src[k + u]);
 #pragma unroll
             for (int u = 0; u < kDropU; ++u)
-                v[u] = __builtin_nontemporal_load((GlobalPtr<const double>)((const double *)src[u] + at));
+                v[u] = drop_load<NT>(src[u], at);
 #pragma unroll
             for (int u = 0; u < kDropU; ++u) acc = acc + v[u];
         }
@@ -266,9 +277,7 @@ __global__ __launch_bounds__(kThrThreads) void k_allreduce_drop(int32_t P, int64
             for (int u = 0; u < kDropU; ++u) src[u] = wave_uniform(s_src[min(k + u, nc - 1)]);
 #pragma unroll
             for (int u = 0; u < kDropU; ++u)
-                if (k + u < nc)
-                    v[u] = __builtin_nontemporal_load(
-                        (GlobalPtr<const double>)((const double *)src[u] + at));
+                if (k + u < nc) v[u] = drop_load<NT>(src[u], at);
 #pragma unroll
             for (int u = 0; u < kDropU; ++u)
                 if (k + u < nc) acc = acc + v[u];
@@ -277,6 +286,9 @@ __global__ __launch_bounds__(kThrThreads) void k_allreduce_drop(int32_t P, int64
     if (e < m) result[e] = acc;
     if (count && blockIdx.x == 0 && tid == 0) *count = total;
 }
+
+constexpr int64_t kDropCached = int64_t(1) << 25;  // elements of all ranks: 256 MiB
+bool drop_cached(int32_t P, int64_t m) { return m <= kDropCached / P; }
 
 // The same for few ranks, whose list costs a workgroup more than its 256
 // elements' sums: at most kDropFewGrid workgroups walk the vector, a test
@@ -289,11 +301,10 @@ __global__ __launch_bounds__(kThrThreads) void k_allreduce_drop(int32_t P, int64
 constexpr int kDropFewU = 8;
 constexpr int64_t kDropFewGrid = 2048;  // eight workgroups per CU
 constexpr int32_t kDropFewRanks = 7;    // the walk at every length
-constexpr int32_t kDropFewRanksHot = 9;               // and up to kDropFewHot
-constexpr int64_t kDropFewHot = int64_t(1) << 25;     // elements of all ranks: 256 MiB
+constexpr int32_t kDropFewRanksHot = 9;  // and while the contributions fit the cache
 
 bool drop_few(int32_t P, int64_t m) {
-    return P <= kDropFewRanks || (P <= kDropFewRanksHot && m <= kDropFewHot / P);
+    return P <= kDropFewRanks || (P <= kDropFewRanksHot && drop_cached(P, m));
 }
 
 __global__ __launch_bounds__(kThrThreads) void k_allreduce_drop_few(
@@ -448,9 +459,9 @@ ecc_status_t ecc_allreduce_drop(int32_t P, int64_t m, const double *const *d_fre
     do {
         const int64_t grid = std::max<int64_t>(
             1, (std::min(m - e0, kDropLaunch) + kThrThreads - 1) / kThrThreads);
-        hipLaunchKernelGGL(k_allreduce_drop, dim3((unsigned)grid), dim3(kThrThreads), 0,
-                           (hipStream_t)hip_stream, P, e0, m, d_fresh, d_arrived, d_result,
-                           e0 == 0 ? d_count : nullptr);
+        hipLaunchKernelGGL(drop_cached(P, m) ? k_allreduce_drop<false> : k_allreduce_drop<true>,
+                           dim3((unsigned)grid), dim3(kThrThreads), 0, (hipStream_t)hip_stream, P,
+                           e0, m, d_fresh, d_arrived, d_result, e0 == 0 ? d_count : nullptr);
         ECC_LAUNCH_CHECK();
         e0 += kDropLaunch;
     } while (e0 < m);

@@ -227,10 +227,10 @@ def test_allreduce_drop_beyond_one_launch(P, m):
 
 @pytest.mark.parametrize("P,m", [(1, 3), (7, 0), (7, 70001), (8, 1 << 20), (9, 3728270),
                                  (8, (1 << 22) + 1), (9, 3728271), (10, 1), (10, 257),
-                                 (16, 100001), (17, 300)])
+                                 (16, 100001), (17, 300), (16, 1 << 21), (16, (1 << 21) + 1)])
 def test_allreduce_drop_ranks(P, m):
-    """The walk of few ranks and the list, at the lengths and rank counts
-    between them: sums in rank order from +0, in place of an arrived rank's
+    """The walk of few ranks and the list with both kinds of loads, at the
+    lengths and rank counts between them: sums in rank order from +0, in place of an arrived rank's
     contribution too, none arrived, infinities, NaN and signed zeros."""
     E = _E()
     announce("drop ranks", P, m)
