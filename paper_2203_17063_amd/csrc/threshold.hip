@@ -76,13 +76,65 @@ __global__ __launch_bounds__(kThrThreads) void k_bcast_prefix(int32_t P, int32_t
     }
 }
 
+// The same in 4,096-element tiles written to every process, for prefixes
+// whose copies leave the Infinity Cache but which make few such tiles: rows
+// that are not 16-byte aligned are stored by 8 bytes there, and the row end is
+// tested per pair.
+constexpr int kBcastPairs = 8;
+constexpr int kBcastTile = 2 * kBcastPairs * kThrThreads;
+
+__global__ __launch_bounds__(kThrThreads) void k_bcast_middle(int32_t P, int32_t root, int64_t k,
+                                                              const double *__restrict__ src,
+                                                              double *const *__restrict__ dst) {
+    const int64_t t0 = (int64_t)blockIdx.x * kBcastTile;
+    const bool src16 = ((uintptr_t)src & 15) == 0;
+    double2 v[kBcastPairs];
+#pragma unroll
+    for (int u = 0; u < kBcastPairs; ++u) {
+        const int64_t e = t0 + 2 * ((int64_t)threadIdx.x + (int64_t)u * kThrThreads);
+        if (e + 1 < k) {
+            if (src16) v[u] = *reinterpret_cast<const double2 *>(src + e);
+            else v[u] = make_double2(src[e], src[e + 1]);
+        } else {
+            v[u] = make_double2(e < k ? src[e] : 0.0, 0.0);
+        }
+    }
+    for (int32_t p = 0; p < P; ++p) {
+        if (p == root) continue;
+        double *__restrict__ d = dst[p];
+        const bool d16 = ((uintptr_t)d & 15) == 0;
+#pragma unroll
+        for (int u = 0; u < kBcastPairs; ++u) {
+            const int64_t e = t0 + 2 * ((int64_t)threadIdx.x + (int64_t)u * kThrThreads);
+            if (e + 1 < k) {
+                if (d16) *reinterpret_cast<double2 *>(d + e) = v[u];
+                else {
+                    d[e] = v[u].x;
+                    d[e + 1] = v[u].y;
+                }
+            } else if (e < k) {
+                d[e] = v[u].x;
+            }
+        }
+    }
+}
+
 // Long prefixes take 4,096-element tiles written to every process; short ones
 // 512-element tiles, their processes split over enough workgroups (at least
-// kBcastRows processes each) to fill the device.  Measured on MI355X: 48 x
-// 22,509 elements 4.1 us, against 28 us in 4,096-element tiles (6
-// workgroups); 32 x 4.2M elements 172-194 us in those (5.5-6.2 TB/s; what
-// the kernel before it left to be written back counts here).
+// kBcastRows processes each) to fill the device; and between kBcastMiddle and
+// kBcastLong, where the copies exceed kBcastCached, k_bcast_middle. Measured
+// on MI355X, us in 512-element tiles / k_bcast_middle / 4,096-element tiles:
+//   16 x   300,000   7.4 /  12.4 /   9.0    200 x   300,000   92 / 114 /  95
+//   32 x 1,000,001  38.0 /  38.2 /  38.2    200 x   500,001  195 / 163 / 159
+//   64 x 1,000,001   116 /    99 /   112    200 x   524,288  171 / 126 / 146
+//   48 x 1,900,001   170 /   147 /   146    200 x 1,000,001  411 / 318 / 349
+//   64 x 2,300,001   301 /   257 /   244     16 x 3,500,000 84.9 / 86.2 / 85.9
+// 48 x 22,509: 4.1 us in 512-element tiles, 28 in 4,096-element ones; 32 x
+// 4.2M: 172-194 us (5.5-6.2 TB/s; what the kernel before it left to be
+// written back counts here).
+constexpr int64_t kBcastMiddle = 400000;          // elements
 constexpr int64_t kBcastLong = int64_t(1) << 21;  // elements: 512 workgroups of long tiles
+constexpr int64_t kBcastCached = int64_t(1) << 25;  // elements of all copies: 256 MiB
 constexpr int32_t kBcastRows = 4;
 constexpr int64_t kBcastFill = 1024;
 
@@ -372,17 +424,21 @@ ecc_status_t ecc_bcast_threshold(int32_t P, int32_t root, int64_t m, double thet
     if (k == 0 || P == 1) return ECC_OK;
     ECC_ARG(d_src != nullptr && d_dst != nullptr, "NULL source or destination array");
     const bool longer = k >= kBcastLong;
-    const int64_t tile = (longer ? 16 : 2) * kThrThreads;
+    const bool middle = !longer && k >= kBcastMiddle && k > kBcastCached / P;
+    const int64_t tile = longer || middle ? kBcastTile : 2 * kThrThreads;
     const int64_t tiles = (k + tile - 1) / tile;
     ECC_ARG(tiles < 0x7fffffff, "too many tiles");
-    const int64_t groups = longer ? 1
-                                  : std::max<int64_t>(1, std::min<int64_t>(kBcastFill / tiles,
-                                                         (P + kBcastRows - 1) / kBcastRows));
+    const int64_t groups = longer || middle ? 1
+                                            : std::max<int64_t>(1, std::min<int64_t>(kBcastFill / tiles,
+                                                                   ((int64_t)P + kBcastRows - 1) / kBcastRows));
     const int32_t per = (int32_t)((P + groups - 1) / groups);
-    const dim3 grid((unsigned)tiles, (unsigned)((P + per - 1) / per));
+    const dim3 grid((unsigned)tiles, (unsigned)(((int64_t)P + per - 1) / per));
     hipStream_t st = (hipStream_t)hip_stream;
-    if (longer)
-        hipLaunchKernelGGL(k_bcast_prefix<8>, grid, dim3(kThrThreads), 0, st, P, root, k, per,
+    if (middle)
+        hipLaunchKernelGGL(k_bcast_middle, grid, dim3(kThrThreads), 0, st, P, root, k, d_src,
+                           d_dst);
+    else if (longer)
+        hipLaunchKernelGGL(k_bcast_prefix<kBcastPairs>, grid, dim3(kThrThreads), 0, st, P, root, k, per,
                            d_src, d_dst);
     else
         hipLaunchKernelGGL(k_bcast_prefix<1>, grid, dim3(kThrThreads), 0, st, P, root, k, per,

@@ -142,9 +142,11 @@ def test_allreduce_drop(P, q):
 
 @pytest.mark.parametrize("P,m,root", [(2, 1, 0), (5, 2, 4), (9, 511, 3), (300, 513, 299),
                                       (6, (1 << 21) - 1, 2), (3, 1 << 21, 0),
-                                      (4, (1 << 21) + 4097, 3)])
+                                      (4, (1 << 21) + 4097, 3), (40, 838860, 7),
+                                      (40, 838861, 7), (84, 399999, 0), (84, 400000, 83),
+                                      (17, (1 << 21) - 1, 0)])
 def test_bcast_and_drop_shapes(P, m, root):
-    """Both tile sizes of the Broadcast at their edges, destinations at both
+    """The Broadcast's tiles at the edges of their lengths, destinations at both
     alignments (rows of m + 1), guards around every row; and the dropping
     allreduce of the same rows (more ranks than one staged list, infinities,
     NaN), bit for bit against sums in rank order."""
