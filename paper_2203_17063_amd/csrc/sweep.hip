@@ -2802,7 +2802,8 @@ static ecc_status_t ecc_matrix_create_impl(ecc_plan_t plan, const ecc_csr_t *A, 
     M->bandwidth = bandwidth;
     M->tile_plane = tile_plane;
     M->tile_rows = tile_rows;
-    M->grid = sweep_grid(M->n_items, kind, layout, M->short_r, colscale, kFormGeneral);
+    M->grid = sweep_grid(M->n_items, kind, layout, M->short_r, colscale,
+                         dia ? kFormDia : kFormGeneral);
     M->dia = dia;
     M->dia_const = dia_const;
     M->dia_val = dia_val;
@@ -2823,12 +2824,12 @@ static ecc_status_t ecc_matrix_create_impl(ecc_plan_t plan, const ecc_csr_t *A, 
     // too, so that every entry point gives the same norm.
     M->tiny = tiny;
     if (M->tiny) M->queue = false;
-    // The static walk keeps the general form's grid, and with it the partial
-    // norms; items claimed from the queue have a partial each, so that there
-    // the grid follows the registers of the form's own kernel.
-    if (M->queue && dia)
-        M->grid = sweep_grid(M->n_items, kind, layout, M->short_r, colscale,
-                             dia_const ? kFormDiaConst : kFormDia);
+    // Constant diagonals keep the grid of value planes under the static walk,
+    // and with it the partial norms; items claimed from the queue have a
+    // partial each, so that there the grid follows the registers of their own
+    // kernel.
+    if (M->queue && dia_const)
+        M->grid = sweep_grid(M->n_items, kind, layout, M->short_r, colscale, kFormDiaConst);
     M->n_part = M->tiny ? n + 1 : M->queue ? M->n_items + 1 : (int64_t)M->grid + 1;
     auto fail = [&](const char *what) {
         set_error("%s", what);

@@ -1128,6 +1128,28 @@ def test_constant_diagonals(kind, offsets, n, P, schedule):
         run.close()
 
 
+def test_static_walk_of_diagonals():
+    """The static walk over diagonals fills the device with its own kernel,
+    whose registers admit more workgroups than the general form's at seven
+    entries per row; constant diagonals walk the same grid, so that norms do
+    not depend on whether the values are kept."""
+    E = _capi()
+    prob = W.jacobi_3d(N=76, T=3, P=5)
+    announce("static walk", prob.n, prob.P)
+    bent = prob.A.val.copy()
+    bent[0] *= 1.25
+    planes = dataclasses.replace(prob, A=W.CSR(prob.n, prob.n, prob.A.row_ptr, prob.A.col, bent))
+    size = {}
+    for name, q, compact in (("constant", prob, 0), ("planes", planes, 0),
+                             ("general", prob, E.ECC_COMPACT_NONE)):
+        run = _iterative(q, schedule=E.ECC_SCHEDULE_STATIC, compact=compact)
+        assert (E.ecc_matrix_diagonal_values(run.mat) is not None) == (name == "constant")
+        size[name] = E.ecc_partials_size(run.mat)
+        run.close()
+    assert size["planes"] > size["general"], size
+    assert size["constant"] == size["planes"], size
+
+
 @pytest.mark.parametrize("kind", ["jacobi", "power"])
 @pytest.mark.parametrize("sizes,P", [((255,), 1), ((1,), 1), ((40001,), 7), ((10000,), 900),
                                      ((129, 255), 3), ((64, 64), 1), ((33, 31), 40),
