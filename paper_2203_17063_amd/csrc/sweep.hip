@@ -1474,16 +1474,19 @@ __global__ void k_build_ell(int64_t n_items, int32_t R, const WorkItem *__restri
 // capped so that as many waves share each SIMD as the row's registers allow
 // without spilling -- 8 for rows of up to 4 entries, 7 for 5, 5 for 7 or 8
 // (the fused Jacobi kernel: 61, 69 and 85-93 VGPRs; 8 waves at R = 5 would
-// spill).
-template <int R, int FORM>
+// spill).  Constant diagonals hold fewer and take 8 under the queue; the
+// static walk, whose grid is that of value planes, keeps their bound, since
+// that of 8 waves leaves 78 scalar registers (60 spilled at R = 7: 41 x 39 x
+// 34 rows, 41 iterations, 393 us per solve against 360).
+template <int R, bool QUEUE, int FORM>
 constexpr int short_waves() {
     if (FORM == kFormDiaPipe) return R >= 7 ? 7 : 8;
-    if (FORM == kFormDiaConst) return 8;
+    if (FORM == kFormDiaConst && QUEUE) return 8;
     return R <= 4 ? 8 : (R == 5 ? 7 : 5);
 }
 template <int KIND, bool STEP, int R, bool QUEUE, int FORM>
 __global__ __launch_bounds__(kSweepThreads)
-__attribute__((amdgpu_waves_per_eu(short_waves<R, FORM>())))
+__attribute__((amdgpu_waves_per_eu(short_waves<R, QUEUE, FORM>())))
 void k_sweep_short(SweepArgs a) {
     if constexpr (FORM == kFormDiaPipe) short_body_pipe<KIND, STEP, R>(a);
     else if constexpr (QUEUE) short_body_queue<KIND, STEP, R, FORM>(a);
