@@ -909,15 +909,17 @@ __global__ __launch_bounds__(kFinishThreads) void k_range_finish(RangeFinishArgs
 // row's end has column -1.
 // In the diagonal forms plane k holds the row's entry on diagonal k (column
 // row + dia.v[k]), and a byte per row (at [base + l]) says which diagonals
-// the row holds: no column indices are stored, and a lane keeps the byte in
-// place of the columns.  Diagonals are in ascending order of offset, so for
-// rows whose entries are sorted by column plane order is CSR order.
+// the row holds: no column indices are stored.  Diagonals are in ascending
+// order of offset, so for rows whose entries are sorted by column plane order
+// is CSR order.  Over value planes a lane forms the columns with the loads of
+// the entries, an item ahead; formed from the mask at the gathers they delay
+// those (1,786,572 rows in a line: 753 us per 31 iterations against 733).
 // With constant diagonals (every entry of diagonal k holds one value,
-// dia_val.v[k]) no planes are stored either: a sweep reads one byte per row
-// of the matrix, 1 in place of 8 R + 1.  The products are those of the
-// stored values, bit for bit.  Measured on MI355X (Jacobi on the 400^3
-// 7-point stencil, 512 ranks): 845 us per iteration against 1,246 with the
-// value planes.
+// dia_val.v[k]) no planes are stored either, and a lane keeps the mask alone:
+// a sweep reads one byte per row of the matrix, 1 in place of 8 R + 1.  The
+// products are those of the stored values, bit for bit.  Measured on MI355X
+// (Jacobi on the 400^3 7-point stencil, 512 ranks): 845 us per iteration
+// against 1,246 with the value planes.
 enum { kFormGeneral = 0, kFormDia = 1, kFormDiaConst = 2, kFormDiaPipe = 3 };
 
 template <int R, int FORM>
@@ -928,20 +930,6 @@ struct EllEntries {
     __device__ __forceinline__ int32_t col(int j, int32_t, const SweepArgs &) const { return c[j]; }
     __device__ __forceinline__ bool diag(int j, int32_t i, const SweepArgs &) const {
         return c[j] == i;
-    }
-    __device__ __forceinline__ double val(int j, const SweepArgs &) const { return v[j]; }
-};
-
-template <int R>
-struct EllEntries<R, kFormDia> {
-    uint32_t mk;
-    double v[R];
-    __device__ __forceinline__ bool held(int j) const { return (mk >> j) & 1u; }
-    __device__ __forceinline__ int32_t col(int j, int32_t i, const SweepArgs &a) const {
-        return i + a.dia.v[j];
-    }
-    __device__ __forceinline__ bool diag(int j, int32_t, const SweepArgs &a) const {
-        return a.dia.v[j] == 0;
     }
     __device__ __forceinline__ double val(int j, const SweepArgs &) const { return v[j]; }
 };
@@ -964,14 +952,18 @@ struct EllEntries<R, kFormDiaConst> {
 template <int R, int FORM>
 __device__ __forceinline__ void ell_entries(const SweepArgs &a, bool live, const WorkItem &w,
                                             int32_t l, EllEntries<R, FORM> &e) {
-    if constexpr (FORM != kFormGeneral) e.mk = live ? a.ell_mask[(int64_t)w.k0 + l] : 0u;
-    if constexpr (FORM != kFormDiaConst) {
+    uint32_t mk = 0;
+    if constexpr (FORM != kFormGeneral) mk = live ? a.ell_mask[(int64_t)w.k0 + l] : 0u;
+    if constexpr (FORM == kFormDiaConst) {
+        e.mk = mk;
+    } else {
         const int64_t base = (int64_t)w.k0 * R + l;
         const int32_t pad = sell_pad(w.nrows);
 #pragma unroll
         for (int j = 0; j < R; ++j) {
             const int64_t k = base + (int64_t)j * pad;
-            if constexpr (FORM == kFormGeneral) e.c[j] = live ? a.ell_col[k] : -1;
+            if constexpr (FORM == kFormDia) e.c[j] = ((mk >> j) & 1u) ? w.row0 + l + a.dia.v[j] : -1;
+            else e.c[j] = live ? a.ell_col[k] : -1;
             e.v[j] = live ? a.ell_val[k] : 0.0;
         }
     }
