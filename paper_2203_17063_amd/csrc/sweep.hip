@@ -92,9 +92,6 @@ struct SweepArgs {
     const double *ell_val;
     const uint8_t *ell_mask;  // short layout, diagonal form: the diagonals of each row
     DiagOffsets dia;          // and their offsets
-    DiagValues dia_val;       // constant diagonals: the value of each
-    const uint16_t *dia_rank; // queue over them: [n_items][kDiagMax] the rank of an item's
-                              // columns, or null
     int64_t ell_n;
     int32_t interleave;  // items dealt round-robin instead of in XCD ranges
     int32_t reserve0;    // workgroup 0 takes no items (grids of kReserveMinGrid or more)
@@ -122,6 +119,15 @@ struct SweepArgs {
     int64_t n_part;
     unsigned *queue;
     int32_t row_part;  // short layout: one partial per row (partials[i] = row i's share)
+};
+
+// What a sweep over constant diagonals takes besides.  The other launches do
+// not carry it: 72 bytes more of arguments cost sweeps of a few microseconds
+// about 1 % (32,161 pages in 10 ranks, 225,127 links: 651 against 638 us per
+// 35 iterations).
+struct DiaArgs : SweepArgs {
+    DiagValues dia_val;        // the value of each diagonal
+    const uint16_t *dia_rank;  // queue: [n_items][kDiagMax] the rank of an item's columns, or null
 };
 
 // Rank state staged in LDS by a fused step.
@@ -922,6 +928,23 @@ __global__ __launch_bounds__(kFinishThreads) void k_range_finish(RangeFinishArgs
 // against 1,246 with the value planes.
 enum { kFormGeneral = 0, kFormDia = 1, kFormDiaConst = 2, kFormDiaPipe = 3 };
 
+// (A trait, not an expression over the forms: the kernel's name holds it, and
+// host and device must give it the same.)
+template <int FORM>
+struct ShortArgsOf {
+    typedef SweepArgs t;
+};
+template <>
+struct ShortArgsOf<kFormDiaConst> {
+    typedef DiaArgs t;
+};
+template <>
+struct ShortArgsOf<kFormDiaPipe> {
+    typedef DiaArgs t;
+};
+template <int FORM>
+using ShortArgs = typename ShortArgsOf<FORM>::t;
+
 template <int R, int FORM>
 struct EllEntries {
     int32_t c[R];
@@ -944,7 +967,7 @@ struct EllEntries<R, kFormDiaConst> {
     __device__ __forceinline__ bool diag(int j, int32_t, const SweepArgs &a) const {
         return a.dia.v[j] == 0;
     }
-    __device__ __forceinline__ double val(int j, const SweepArgs &a) const {
+    __device__ __forceinline__ double val(int j, const DiaArgs &a) const {
         return a.dia_val.v[j];
     }
 };
@@ -974,7 +997,7 @@ __device__ __forceinline__ void ell_entries(const SweepArgs &a, bool live, const
 // on the item's descriptor, so while the gathers of item n are in flight
 // the entries of item n + 1 are loaded (and the descriptor of item n + 2).
 template <int KIND, bool STEP, int R, int FORM>
-__device__ __forceinline__ void short_body(const SweepArgs &a) {
+__device__ __forceinline__ void short_body(const ShortArgs<FORM> &a) {
     __shared__ double s_red[kSweepThreads / 64];
     __shared__ uint8_t s_eff[STEP ? kFusedMaxP : 1];
     __shared__ int32_t s_bs[STEP ? kFusedMaxP + 1 : 1];
@@ -1090,7 +1113,7 @@ __device__ __forceinline__ int xcc_id() {
 // the workgroup through LDS at the one barrier per item, where the item's
 // partial norm is also assembled.
 template <int KIND, bool STEP, int R, int FORM>
-__device__ __forceinline__ void short_body_queue(const SweepArgs &a) {
+__device__ __forceinline__ void short_body_queue(const ShortArgs<FORM> &a) {
     __shared__ double s_red[kSweepThreads / 64];
     __shared__ double s_ws[2][kSweepThreads / 64];
     __shared__ int32_t s_tk[5];  // [0..1] tickets handed on per item, [2..4] the first three
@@ -1224,13 +1247,13 @@ __device__ __forceinline__ WorkItem uniform_item(const WorkItem &v) {
 // scalar registers (one cached scalar load each), where the arguments kept
 // over the loop overflow them (up to 150 spilled to vector lanes, one vector
 // instruction per use).
-typedef const __attribute__((address_space(4))) SweepArgs *KernArgs;
+typedef const __attribute__((address_space(4))) DiaArgs *KernArgs;
 __device__ __forceinline__ KernArgs kernel_args() {
     return (KernArgs)__builtin_amdgcn_kernarg_segment_ptr();
 }
-__device__ __forceinline__ const SweepArgs &item_args(KernArgs &k) {
+__device__ __forceinline__ const DiaArgs &item_args(KernArgs &k) {
     asm volatile("" : "+s"(k));
-    return *(const SweepArgs *)k;
+    return *(const DiaArgs *)k;
 }
 
 // The queue over constant diagonals, gathers one item ahead.  A row holds a
@@ -1264,7 +1287,7 @@ struct ShortGathers {
 struct ShortMasks {
     uint32_t mk, rk;
 };
-__device__ __forceinline__ ShortMasks pipe_masks(const SweepArgs &a, int32_t w, const WorkItem &it,
+__device__ __forceinline__ ShortMasks pipe_masks(const DiaArgs &a, int32_t w, const WorkItem &it,
                                                  int tid) {
     ShortMasks m;
     m.mk = (a.ell_mask + it.k0)[min(tid, it.nrows - 1)];
@@ -1280,7 +1303,7 @@ __device__ __forceinline__ ShortMasks pipe_masks(const SweepArgs &a, int32_t w, 
 // their middle, as stencils have them (a.dia_rank is null for other sets,
 // which take short_body_queue).
 template <int KIND, bool STEP, int R>
-__device__ __forceinline__ void pipe_gather(const SweepArgs &a, const WorkItem &w, int tid,
+__device__ __forceinline__ void pipe_gather(const DiaArgs &a, const WorkItem &w, int tid,
                                             const ShortMasks &m, const uint8_t *s_eff,
                                             const StepView &sv, RankCache &rc,
                                             ShortGathers<R> &g) {
@@ -1351,7 +1374,7 @@ struct TicketWalk {
 };
 
 template <int KIND, bool STEP, int R>
-__device__ __forceinline__ void short_body_pipe(const SweepArgs &a) {
+__device__ __forceinline__ void short_body_pipe(const DiaArgs &a) {
     __shared__ double s_red[kSweepThreads / 64];
     __shared__ double s_ws[2][kSweepThreads / 64];
     __shared__ int32_t s_tk[6];  // [0..1] tickets handed on per item, [2..5] the first four
@@ -1381,7 +1404,7 @@ __device__ __forceinline__ void short_body_pipe(const SweepArgs &a) {
     int kk = 0;
     KernArgs kargs = kernel_args();
     while (w0 >= 0) {
-        const SweepArgs &a = item_args(kargs);
+        const DiaArgs &a = item_args(kargs);
         int32_t tk = -1;
         if (tid == 0) tk = tickets.next(a.queue, a.n_items);
         const WorkItem i3 = a.items[w3 >= 0 ? w3 : last];
@@ -1479,7 +1502,7 @@ constexpr int short_waves() {
 template <int KIND, bool STEP, int R, bool QUEUE, int FORM>
 __global__ __launch_bounds__(kSweepThreads)
 __attribute__((amdgpu_waves_per_eu(short_waves<R, QUEUE, FORM>())))
-void k_sweep_short(SweepArgs a) {
+void k_sweep_short(ShortArgs<FORM> a) {
     if constexpr (FORM == kFormDiaPipe) short_body_pipe<KIND, STEP, R>(a);
     else if constexpr (QUEUE) short_body_queue<KIND, STEP, R, FORM>(a);
     else short_body<KIND, STEP, R, FORM>(a);
@@ -2233,7 +2256,7 @@ static int32_t sweep_grid(int64_t n_items, int kind, int layout, int32_t short_r
 // The short-row kernel of a matrix's row class.
 template <int K, bool S, bool Q, int F>
 static void launch_short(ecc_matrix_t M, dim3 grid, dim3 block, hipStream_t st,
-                         const SweepArgs &a) {
+                         const DiaArgs &a) {
     switch (short_class(M->short_r)) {
         case 3: hipLaunchKernelGGL((k_sweep_short<K, S, 3, Q, F>), grid, block, 0, st, a); break;
         case 4: hipLaunchKernelGGL((k_sweep_short<K, S, 4, Q, F>), grid, block, 0, st, a); break;
@@ -2248,7 +2271,7 @@ static void launch_short(ecc_matrix_t M, dim3 grid, dim3 block, hipStream_t st,
 // never built.
 template <int K, bool S>
 static void launch_layout(ecc_matrix_t M, dim3 grid, dim3 block, hipStream_t st,
-                          const SweepArgs &a) {
+                          const DiaArgs &a) {
     if (K == ECC_KIND_POWER && !S && M->colscale) {
         if (M->layout == kLaySorted)
             hipLaunchKernelGGL((k_sweep<ECC_KIND_POWER, false, kLaySorted, true>), grid, block, 0,
@@ -2278,7 +2301,7 @@ static void launch_layout(ecc_matrix_t M, dim3 grid, dim3 block, hipStream_t st,
 
 ecc_status_t launch_sweep(ecc_matrix_t M, const SweepLaunch &L) {
     ecc_plan_t pl = M->plan;
-    SweepArgs a{};
+    DiaArgs a{};
     a.items = M->d_items;
     a.n_items = (int32_t)M->n_items;
     const bool sorted = M->layout == kLaySorted || M->layout == kLayRanges;
