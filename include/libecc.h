@@ -368,6 +368,18 @@ ecc_status_t ecc_matrix_diagonal_values(ecc_matrix_t A, int32_t *constant, doubl
  * ECC_SCHEDULE_QUEUE or ECC_SCHEDULE_SINGLE. */
 ecc_status_t ecc_matrix_schedule(ecc_matrix_t A, int32_t *schedule);
 
+/* The kernel that sweeps this matrix (host only), where its layout, form and
+ * schedule leave a choice: ECC_SWEEP_PIPELINED, the queue over constant
+ * diagonals that gathers for an item while another is finished (as many
+ * diagonals as the row class R, for Jacobi the main one in their middle);
+ * ECC_SWEEP_GATHER_FIRST, stream rows whose products are staged before the
+ * rows are summed; else ECC_SWEEP_PLAIN.  *workgroups (may be NULL): those of
+ * a launch. */
+#define ECC_SWEEP_PLAIN 0
+#define ECC_SWEEP_PIPELINED 1
+#define ECC_SWEEP_GATHER_FIRST 2
+ecc_status_t ecc_matrix_sweep(ecc_matrix_t A, int32_t *sweep, int32_t *workgroups);
+
 /* The layout ecc_matrix_create chose (ECC_LAYOUT_*) and, for
  * ECC_LAYOUT_SHORT, the entries held per row R, for ECC_LAYOUT_RANGES the
  * number of column ranges (0 otherwise).  Host only. */

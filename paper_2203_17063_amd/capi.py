@@ -26,6 +26,7 @@ ECC_THRESHOLD_DATA, ECC_THRESHOLD_PROCS = 0, 1
 ECC_LAYOUT_STREAM, ECC_LAYOUT_SORTED, ECC_LAYOUT_SHORT, ECC_LAYOUT_RANGES = 0, 1, 2, 3
 ECC_SCHEDULE_AUTO, ECC_SCHEDULE_STATIC, ECC_SCHEDULE_QUEUE, ECC_SCHEDULE_SINGLE = 0, 1, 2, 3
 ECC_COMPACT_AUTO, ECC_COMPACT_NONE = 0, 1
+ECC_SWEEP_PLAIN, ECC_SWEEP_PIPELINED, ECC_SWEEP_GATHER_FIRST = 0, 1, 2
 ECC_FORM_GENERAL, ECC_FORM_COLUMN_VALUES, ECC_FORM_DIAGONALS = 0, 1, 2
 ECC_MAX_DIAGONALS = 8
 ECC_SCRATCH_DOUBLES = 1 << 20
@@ -79,6 +80,7 @@ _SIGS = [
     ("ecc_matrix_destroy", ctypes.c_int, [_VP]),
     ("ecc_matrix_tiling", ctypes.c_int, [_VP, _VP, _VP]),
     ("ecc_matrix_schedule", ctypes.c_int, [_VP, _VP]),
+    ("ecc_matrix_sweep", ctypes.c_int, [_VP, _VP, _VP]),
     ("ecc_matrix_form", ctypes.c_int, [_VP, _VP, _VP, _VP]),
     ("ecc_matrix_diagonal_values", ctypes.c_int, [_VP, _VP, _VP]),
     ("ecc_partials_size", _I64, [_VP]),
@@ -266,6 +268,13 @@ def ecc_matrix_schedule(mat) -> int:
     sch = ctypes.c_int32(0)
     _check(lib().ecc_matrix_schedule(mat, ctypes.byref(sch)))
     return sch.value
+
+
+def ecc_matrix_sweep(mat):
+    """(kernel, workgroups) of a sweep."""
+    sweep, groups = ctypes.c_int32(0), ctypes.c_int32(0)
+    _check(lib().ecc_matrix_sweep(mat, ctypes.byref(sweep), ctypes.byref(groups)))
+    return sweep.value, groups.value
 
 
 def ecc_matrix_form(mat):

@@ -441,7 +441,7 @@ struct ecc_matrix_s {
     int64_t n_rfix = 0;
     int32_t *d_ell_col = nullptr;   // short layout: entries item by item, entry-major (-1: padding)
     uint8_t *d_ell_mask = nullptr;  // short layout, diagonal form: the diagonals each row holds
-    uint16_t *d_dia_rank = nullptr;  // queue: the rank of each item's columns by diagonal
+    uint16_t *d_dia_rank = nullptr;  // pipe: the rank of each item's columns by diagonal
     bool dia = false;               // short layout in diagonal form (d_ell_mask, no d_ell_col)
     int32_t n_dia = 0;              // its diagonals
     ecc::DiagOffsets dia_off{};     // their offsets, ascending
@@ -453,6 +453,7 @@ struct ecc_matrix_s {
     double *d_partials = nullptr;   // internal partials of ecc_solve: 2 x n_part
     int64_t n_part = 1;             // partial sums a sweep writes: grid + 1, or n_items + 1 (queue)
     bool queue = false;             // short layout: items claimed from a run-time queue
+    bool pipe = false;              // queue over constant diagonals: the pipelined one
     bool tiny = false;              // short layout: ecc_solve runs as one single-workgroup launch;
                                     // sweeps write one partial per row (n_part = n + 1)
     unsigned *d_queue = nullptr;    // its ticket counters, (kQueueRanges + 1) x kQueueStride

@@ -127,7 +127,7 @@ struct SweepArgs {
 // 35 iterations).
 struct DiaArgs : SweepArgs {
     DiagValues dia_val;        // the value of each diagonal
-    const uint16_t *dia_rank;  // queue: [n_items][kDiagMax] the rank of an item's columns, or null
+    const uint16_t *dia_rank;  // pipe: [n_items][kDiagMax] the rank of an item's columns
 };
 
 // Rank state staged in LDS by a fused step.
@@ -1300,8 +1300,7 @@ __device__ __forceinline__ ShortMasks pipe_masks(const DiaArgs &a, int32_t w, co
 // diagonal's 64 columns are consecutive elements of one vector: its base is
 // uniform, and neither the rank of each column nor a row's mask is looked at
 // (most waves of a stencil).  Compiled for R diagonals, Jacobi's main one in
-// their middle, as stencils have them (a.dia_rank is null for other sets,
-// which take short_body_queue).
+// their middle, as stencils have them (other sets take short_body_queue).
 template <int KIND, bool STEP, int R>
 __device__ __forceinline__ void pipe_gather(const DiaArgs &a, const WorkItem &w, int tid,
                                             const ShortMasks &m, const uint8_t *s_eff,
@@ -2187,13 +2186,13 @@ static hipError_t sweep_occupancy(int *per_cu, int kind, bool colscale) {
                      per_cu, k_sweep<ECC_KIND_POWER, S, LAY>, kSweepThreads, 0);
 }
 
-template <int R, int FORM>
+template <int R, bool QUEUE, int FORM>
 static hipError_t short_occupancy_r(int *per_cu, int kind) {
     return kind == ECC_KIND_JACOBI
                ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                     per_cu, k_sweep_short<ECC_KIND_JACOBI, true, R, false, FORM>, kSweepThreads, 0)
+                     per_cu, k_sweep_short<ECC_KIND_JACOBI, true, R, QUEUE, FORM>, kSweepThreads, 0)
                : hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                     per_cu, k_sweep_short<ECC_KIND_POWER, true, R, false, FORM>, kSweepThreads, 0);
+                     per_cu, k_sweep_short<ECC_KIND_POWER, true, R, QUEUE, FORM>, kSweepThreads, 0);
 }
 
 // Entries per row of the short-layout kernel that serves rows of at most
@@ -2202,15 +2201,21 @@ static int short_class(int32_t max_row) {
     return max_row <= 3 ? 3 : max_row == 4 ? 4 : max_row == 5 ? 5 : max_row <= 7 ? 7 : 8;
 }
 
-template <int FORM>
+template <bool QUEUE, int FORM>
 static hipError_t short_occupancy(int *per_cu, int kind, int32_t short_r) {
     switch (short_class(short_r)) {
-        case 3: return short_occupancy_r<3, FORM>(per_cu, kind);
-        case 4: return short_occupancy_r<4, FORM>(per_cu, kind);
-        case 5: return short_occupancy_r<5, FORM>(per_cu, kind);
-        case 7: return short_occupancy_r<7, FORM>(per_cu, kind);
-        default: return short_occupancy_r<8, FORM>(per_cu, kind);
+        case 3: return short_occupancy_r<3, QUEUE, FORM>(per_cu, kind);
+        case 4: return short_occupancy_r<4, QUEUE, FORM>(per_cu, kind);
+        case 5: return short_occupancy_r<5, QUEUE, FORM>(per_cu, kind);
+        case 7: return short_occupancy_r<7, QUEUE, FORM>(per_cu, kind);
+        default: return short_occupancy_r<8, QUEUE, FORM>(per_cu, kind);
     }
+}
+
+// The sets of diagonals short_body_pipe is compiled for: R of them, Jacobi's
+// main one in their middle.
+static bool dia_piped(int kind, int R, int32_t n_dia, const DiagOffsets &off) {
+    return n_dia == R && (kind != ECC_KIND_JACOBI || off.v[R / 2] == 0);
 }
 
 // The workgroups' values of each diagonal (k_diag_values) as one, or false
@@ -2232,6 +2237,11 @@ static bool merge_diag_values(int blocks, const unsigned long long *rep, const u
     return true;
 }
 
+// Workgroups of a sweep: those the device holds together, at most one per
+// item.  Value planes and the general form ask for the static walk's kernel
+// under the queue too (over value planes of seven entries its own holds one
+// workgroup per CU fewer); constant diagonals ask here for the queue's kernel
+// that runs.
 static int32_t sweep_grid(int64_t n_items, int kind, int layout, int32_t short_r,
                           bool colscale, int form) {
     int dev = 0, cus = 0, per_cu = 0;
@@ -2241,11 +2251,12 @@ static int32_t sweep_grid(int64_t n_items, int kind, int layout, int32_t short_r
     const hipError_t e =
         layout == kLaySorted   ? sweep_occupancy<kLaySorted>(&per_cu, kind, colscale)
         : layout == kLayRanges ? sweep_occupancy<kLayRanges>(&per_cu, kind, colscale)
-        : layout == kLayShort  ? (form == kFormDiaConst ? short_occupancy<kFormDiaConst>(&per_cu, kind, short_r)
-                                  : form == kFormDia
-                                      ? short_occupancy<kFormDia>(&per_cu, kind, short_r)
-                                      : short_occupancy<kFormGeneral>(&per_cu, kind, short_r))
-                               : sweep_occupancy<kLayStream>(&per_cu, kind, false);
+        : layout == kLayShort
+            ? (form == kFormDiaPipe    ? short_occupancy<true, kFormDiaPipe>(&per_cu, kind, short_r)
+               : form == kFormDiaConst ? short_occupancy<true, kFormDiaConst>(&per_cu, kind, short_r)
+               : form == kFormDia      ? short_occupancy<false, kFormDia>(&per_cu, kind, short_r)
+                                       : short_occupancy<false, kFormGeneral>(&per_cu, kind, short_r))
+            : sweep_occupancy<kLayStream>(&per_cu, kind, false);
     if (e != hipSuccess || per_cu < 1) per_cu = 4;
     const int64_t resident = (int64_t)std::max(cus, 1) * per_cu;
     int64_t g = std::max<int64_t>(1, std::min<int64_t>({n_items, resident, (int64_t)kMaxSweepBlocks}));
@@ -2285,7 +2296,7 @@ static void launch_layout(ecc_matrix_t M, dim3 grid, dim3 block, hipStream_t st,
         if constexpr (!S) hipLaunchKernelGGL((k_sweep<K, S, kLayRanges>), grid, block, 0, st, a);
     } else if (M->layout == kLayShort) {
         if (M->queue) {
-            if (M->d_dia_rank) launch_short<K, S, true, kFormDiaPipe>(M, grid, block, st, a);
+            if (M->pipe) launch_short<K, S, true, kFormDiaPipe>(M, grid, block, st, a);
             else if (M->dia_const) launch_short<K, S, true, kFormDiaConst>(M, grid, block, st, a);
             else if (M->dia) launch_short<K, S, true, kFormDia>(M, grid, block, st, a);
             else launch_short<K, S, true, kFormGeneral>(M, grid, block, st, a);
@@ -2844,10 +2855,12 @@ static ecc_status_t ecc_matrix_create_impl(ecc_plan_t plan, const ecc_csr_t *A, 
     if (M->tiny) M->queue = false;
     // Constant diagonals keep the grid of value planes under the static walk,
     // and with it the partial norms; items claimed from the queue have a
-    // partial each, so that there the grid follows the registers of their own
-    // kernel.
+    // partial each, so that there the grid follows the registers of the kernel
+    // that runs.
+    M->pipe = M->queue && dia_const && dia_piped(kind, short_class(M->short_r), n_dia, dia_off);
     if (M->queue && dia_const)
-        M->grid = sweep_grid(M->n_items, kind, layout, M->short_r, colscale, kFormDiaConst);
+        M->grid = sweep_grid(M->n_items, kind, layout, M->short_r, colscale,
+                             M->pipe ? kFormDiaPipe : kFormDiaConst);
     M->n_part = M->tiny ? n + 1 : M->queue ? M->n_items + 1 : (int64_t)M->grid + 1;
     auto fail = [&](const char *what) {
         set_error("%s", what);
@@ -2928,9 +2941,7 @@ static ecc_status_t ecc_matrix_create_impl(ecc_plan_t plan, const ecc_csr_t *A, 
                                      sizeof(double) * R * short_rows_total) != hipSuccess))
             return fail("hipMalloc of the item-major entries failed");
         const int blocks = (int)std::min<int64_t>(65536, M->n_items);
-        // the sets of diagonals short_body_pipe is compiled for
-        if (dia_const && M->queue && n_dia == R &&
-            (kind != ECC_KIND_JACOBI || dia_off.v[R / 2] == 0)) {
+        if (M->pipe) {
             if (hipMalloc((void **)&M->d_dia_rank, sizeof(uint16_t) * kDiagMax * M->n_items) !=
                 hipSuccess)
                 return fail("hipMalloc of the items' column ranks failed");
@@ -3060,6 +3071,17 @@ ecc_status_t ecc_matrix_diagonal_values(ecc_matrix_t M, int32_t *constant, doubl
     if (values)
         for (int k = 0; k < ECC_MAX_DIAGONALS; ++k)
             values[k] = (M->dia_const && k < M->n_dia) ? M->dia_val.v[k] : 0.0;
+    return ECC_OK;
+}
+
+ecc_status_t ecc_matrix_sweep(ecc_matrix_t M, int32_t *sweep, int32_t *workgroups) {
+    clear_error();
+    ECC_ARG(M != nullptr, "matrix is NULL");
+    ECC_ARG(sweep != nullptr, "NULL output");
+    if (workgroups) *workgroups = M->grid;
+    *sweep = M->pipe                     ? ECC_SWEEP_PIPELINED
+             : M->layout == kLayStream ? ECC_SWEEP_GATHER_FIRST
+                                         : ECC_SWEEP_PLAIN;
     return ECC_OK;
 }
 

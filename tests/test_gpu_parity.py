@@ -1128,6 +1128,62 @@ def test_constant_diagonals(kind, offsets, n, P, schedule):
         run.close()
 
 
+@pytest.mark.parametrize("kind,offsets,piped", [
+    ("jacobi", [-40, -1, 0, 1], True), ("jacobi", [-40, 0, 1, 2], False),
+    ("jacobi", [-900, -30, -1, -2000, 0, 1, 30, 900], True),
+    ("jacobi", [-900, -30, -1, 0, 1, 30, 900, 2000], False),
+    ("jacobi", [-30, -1, 0, 1, 2, 30], False), ("jacobi", [-3, -2, -1, 0, 1, 2, 3], True),
+    ("jacobi", [-5, -4, -3, -2, -1, 0, 1], False), ("jacobi", [-700, -2, 0, 1, 700], True),
+    ("power", [1, 2, 700, 5000], True), ("power", [-900, -30, -1, 0, 1, 30, 900, 2000], True),
+    ("power", [0, 1, 2, 3, 4, 5], False)])
+def test_pipelined_sets_of_diagonals(kind, offsets, piped):
+    """Which sets of constant diagonals the pipelined queue takes: as many as
+    the row class, Jacobi's main one in their middle, even classes too; the
+    oracle's iterates either way, and launches no larger than the kernel's own
+    occupancy."""
+    E = _capi()
+    offsets, n, P = sorted(offsets), 20011, 9
+    announce("pipelined sets", kind, offsets)
+    values = [0.125 / (k + 2) for k in range(len(offsets))]
+    if kind == "jacobi":
+        values[offsets.index(0)] = 2.5
+    prob = _constant_diagonals(_offset_subset_problem(kind, n, offsets, P, seed=len(offsets)),
+                               offsets, values)
+    kw = {"schedule": E.ECC_SCHEDULE_QUEUE}
+    run = _iterative(prob, **kw)
+    assert E.ecc_matrix_diagonal_values(run.mat) == values
+    assert E.ecc_matrix_sweep(run.mat)[0] == (E.ECC_SWEEP_PIPELINED if piped
+                                              else E.ECC_SWEEP_PLAIN)
+    run.close()
+    _solve_and_compare(prob, bitwise=True, form=E.ECC_FORM_DIAGONALS, solves=2, **kw)
+
+
+def test_pipelined_grid_is_its_kernels():
+    """The pipelined queue launches what the device holds of its own kernel:
+    seven workgroups per CU at eight diagonals, where the queue over constant
+    diagonals that is not pipelined holds eight."""
+    E = _capi()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    n, size = 2100 * 256, {}
+    for name, offsets in (("pipelined", [-900, -60, -30, -1, 0, 1, 30, 900]),
+                          ("plain", [-900, -60, -30, 0, 1, 2, 30, 900])):
+        announce("pipelined grid", name)
+        cols = np.arange(n)[:, None] + np.array(offsets)
+        held = (cols >= 0) & (cols < n)
+        rp = np.zeros(n + 1, dtype=np.int32)
+        rp[1:] = np.cumsum(held.sum(1))
+        val = np.where(np.array(offsets) == 0, 4.0, 0.25)
+        A = W.CSR(n, n, rp, cols[held].astype(np.int32), np.broadcast_to(val, held.shape)[held])
+        counts = np.array([n])
+        prob = W.Iterative("full-diagonals", "jacobi", A, counts, W.exclusive_scan(counts), 0,
+                           np.ones((1, 1), dtype=np.uint8), 1, np.zeros(n), b=np.ones(n), norm=2)
+        run = _iterative(prob, schedule=E.ECC_SCHEDULE_QUEUE)
+        size[name] = E.ecc_matrix_sweep(run.mat)
+        run.close()
+    assert size["pipelined"] == (E.ECC_SWEEP_PIPELINED, 7 * cus), size
+    assert size["plain"] == (E.ECC_SWEEP_PLAIN, 8 * cus), size
+
+
 def test_static_walk_of_diagonals():
     """The static walk over diagonals fills the device with its own kernel,
     whose registers admit more workgroups than the general form's at seven
@@ -1191,6 +1247,10 @@ def test_queue_of_constant_diagonals(kind, sizes, P):
     outs = []
     for compact in (E.ECC_COMPACT_AUTO, E.ECC_COMPACT_NONE):
         run = _iterative(prob, compact=compact, **kw)
+        # (one row holds one diagonal of the three its kernel is compiled for)
+        piped = compact == E.ECC_COMPACT_AUTO and n > 1
+        assert E.ecc_matrix_sweep(run.mat)[0] == (E.ECC_SWEEP_PIPELINED if piped
+                                                  else E.ECC_SWEEP_PLAIN)
         run.solve(histories=True)
         torch.cuda.synchronize()
         outs.append((run.d_x.cpu().numpy(), run.d_x_hat.cpu().numpy(),
