@@ -425,6 +425,7 @@ struct ecc_matrix_s {
     bool irregular = false;         // row lengths vary widely: sorted layout, items dealt round-robin
     int layout = 0;                 // kLayStream, kLaySorted or kLayShort
     int32_t short_r = ecc::kShortRow;  // short layout: entries per row the kernel holds (>= longest row)
+    bool gather_first = false;      // stream layout: products staged before the rows are summed
     int64_t bandwidth = 0;          // max |col - row|
     int32_t *d_order = nullptr;     // sorted layout: the row at each sorted position, [n]
     int32_t *d_srow_ptr = nullptr;  // sorted layout: row pointers of the sorted copy, [n + 1]

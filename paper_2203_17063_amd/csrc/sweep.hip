@@ -193,7 +193,7 @@ __device__ __forceinline__ double view_load(int32_t c, int32_t lo, int32_t hi,
 // Lanes per row of a stream item: rows of at most 16 nonzeros on average are
 // summed by one lane in CSR order; longer ones by up to 64 lanes, keeping at
 // least 8 nonzeros per lane.
-__device__ __forceinline__ int lanes_per_row(int32_t nnz, int32_t nr) {
+__host__ __device__ __forceinline__ int lanes_per_row(int32_t nnz, int32_t nr) {
     int tpr = 1;
     if (nnz > 16 * nr)
         while (tpr < 64 && tpr * 2 * nr <= kSweepThreads && nnz >= 16 * tpr * nr) tpr *= 2;
@@ -398,19 +398,17 @@ __device__ __forceinline__ double stream_compute(const WorkItem &it, int32_t rp0
     }
 }
 
-// Stream items gathered first (kGatherFirst): each thread gathers for the
-// eight nonzeros it loaded, all in flight together, and stages the products;
-// the rows are then sums over LDS, by the same lanes in the same order as
-// stream_compute's.  With the gathers inside the row sums a lane waits for
-// one memory latency per entry.  Measured on MI355X, Jacobi over 300,000 rows
-// of 12 to 48 entries, 24 ranks: 53 us per iteration against 78 (at four waves
-// per SIMD; five, with fewer registers, were 12 % slower).  The sorted layout keeps the
+// Stream items gathered first: each thread gathers for the eight nonzeros it
+// loaded, all in flight together, and stages the products; the rows are then
+// sums over LDS, by the same lanes in the same order as stream_compute's.
+// With the gathers inside the row sums a lane waits for one memory latency
+// per entry, but the 64 lanes of a gather read the k-th entries of 64 rows,
+// which lie close together where rows are alike and near the diagonal
+// (rows_alike says which matrices are swept by row sums).  The sorted layout keeps the
 // other order (PageRank on 150,000 pages, 2.1M links: 27 us per iteration
 // against 29 gathered first: it has about one item per workgroup, and with
 // the smaller LDS share more of them start together), and so does the range
 // layout, whose items mix rank blocks.
-template <int LAY>
-constexpr bool kGatherFirst = LAY == kLayStream;
 
 // Jacobi: the item's row pointers and, after stream_gather, its rows'
 // diagonal entries.
@@ -580,11 +578,11 @@ __device__ __forceinline__ void sweep_prologue(const SweepArgs &a, uint8_t *s_ef
 // its sorted copy (kLaySorted) or over its sub-rows cut by column range
 // (kLayRanges); all may contain vector items and pieces.
 // The short-row layout has its own body.
-template <int KIND, bool STEP, int LAY, bool CS>
+template <int KIND, bool STEP, int LAY, bool CS, bool GF>
 __device__ __forceinline__ void sweep_body(const SweepArgs &a) {
     static_assert(LAY == kLayStream || LAY == kLaySorted || LAY == kLayRanges,
                   "stream layouts only");
-    constexpr bool GF = kGatherFirst<LAY>;
+    static_assert(!GF || LAY == kLayStream, "stream rows only are gathered first");
     // padded by 8 so that a row's first eight entries can be read unclamped;
     // gather-first items stage their products in s_val instead
     __shared__ int32_t s_col[GF ? 1 : kStreamCap + 8];
@@ -689,9 +687,9 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a) {
     if (tid == 0) a.partials[blockIdx.x] = total;
 }
 
-template <int KIND, bool STEP, int LAY, bool CS = false>
+template <int KIND, bool STEP, int LAY, bool CS = false, bool GF = false>
 __global__ __launch_bounds__(kSweepThreads) void k_sweep(SweepArgs a) {
-    sweep_body<KIND, STEP, LAY, CS>(a);
+    sweep_body<KIND, STEP, LAY, CS, GF>(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -1893,6 +1891,80 @@ static void build_items(const std::vector<int32_t> &rp, const std::vector<int64_
     items.insert(items.end(), stream.begin(), stream.end());
 }
 
+// The entries whose column lies outside their row's rank block.
+__global__ void k_off_block(int64_t n_rows, const int32_t *__restrict__ row_ptr,
+                            const int32_t *__restrict__ col, int32_t P,
+                            const int32_t *__restrict__ block_start,
+                            unsigned long long *__restrict__ off) {
+    unsigned long long mine = 0;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_rows;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        int32_t a = 0, z = P;  // block_start[a] <= i < block_start[z]
+        while (z - a > 1) {
+            const int32_t mid = (a + z) >> 1;
+            if (block_start[mid] <= i) a = mid;
+            else z = mid;
+        }
+        const int32_t lo = block_start[a], hi = block_start[a + 1];
+        for (int32_t k = row_ptr[i]; k < row_ptr[i + 1]; ++k) {
+            const int32_t c = col[k];
+            mine += c < lo || c >= hi;
+        }
+    }
+    if (mine) atomicAdd(off, mine);
+}
+
+// How a matrix's stream items look to their row sums, on average over the
+// entries: the gathers the lanes of an item's longest row make one after the
+// other (a row of one lane has its first eight in flight together), the
+// longest row over the mean one, and whether most items have one lane per row.
+struct StreamShape {
+    double chain = 0.0, spread = 0.0;
+    bool one_lane = false;
+};
+static StreamShape stream_shape(const std::vector<int32_t> &rp,
+                                const std::vector<WorkItem> &items) {
+    double chain = 0.0, spread = 0.0, all = 0.0, one = 0.0;
+    for (const WorkItem &it : items) {
+        const int32_t nnz = it.k1 - it.k0;
+        if (it.kind != kItemStream || nnz == 0) continue;
+        int32_t longest = 0;
+        for (int32_t r = it.row0; r < it.row0 + it.nrows; ++r)
+            longest = std::max(longest, rp[r + 1] - rp[r]);
+        const int lanes = lanes_per_row(nnz, it.nrows);
+        chain += (double)nnz * (lanes == 1 ? 1 + std::max(0, longest - 8)
+                                           : (longest + lanes - 1) / lanes);
+        spread += (double)longest * it.nrows;
+        all += nnz;
+        if (lanes == 1) one += nnz;
+    }
+    if (all == 0.0) return {};
+    return {chain / all, spread / all, 2.0 * one > all};
+}
+
+// Which stream rows are gathered first: all but rows that are alike, make few
+// gathers in turn and stay in their own rank's block (a gather from another
+// looks its rank up), whose sums read the k-th entries of 64 rows together.
+// Measured on MI355X, Jacobi, us per iteration gathered first / in the row
+// sums, rows of lo to hi entries, columns normal around the row with the
+// deviation in brackets:
+//   300,007 rows, 12-48 [1500], 6 ranks     47 /  68   (chain 24, spread 1.6)
+//   450,001 rows, 20-32 [1500], 6 ranks     57 /  60   (chain 16, spread 1.2)
+//   300,007 rows, 15-17 [4000], 24 ranks    38 /  44   (chain 10, one lane)
+//   300,007 rows, 22-24 [15000], 24 ranks   49 /  61   (chain 12, half outside)
+//   450,001 rows, 18-20 [1500], 6 ranks     46 /  40   (chain 10, 1 % outside)
+//   120,001 rows,  9-10 [300], 24 ranks     21 /  17   (chain 3, one lane)
+// Over 2,765 matrices of 2,000 to 500,000 rows of 9 to 60 entries, 1 to 128
+// ranks, the order chosen is within 3 % of the faster one in all but 52 (14 %
+// at most); gathering first throughout takes up to 1.28 times the faster one's
+// time, the row sums up to 2.9 times.
+constexpr double kSumsChain = 12.0, kSumsChainOneLane = 5.0;  // row sums below
+constexpr double kSumsSpread = 1.15;
+constexpr double kSumsOff = 0.3;  // share of the entries outside their row's block
+static bool rows_alike(const StreamShape &s) {
+    return s.spread < kSumsSpread && s.chain < (s.one_lane ? kSumsChainOneLane : kSumsChain);
+}
+
 // Short-row layout: runs of up to kSweepThreads rows of one rank.  With
 // plane tiling (plane B > 0, tile W > 0) the runs are taken segment by
 // segment, tile by tile: for tau = 0, W, 2W, ... below B and every plane z,
@@ -2171,7 +2243,7 @@ __global__ void k_sort_rows(int32_t n, const int32_t *__restrict__ order,
 // item, rounded down to a multiple of the 8 XCDs.
 // Occupancy of the kernel a loop iteration launches: the fused one, except
 // for the sorted and range layouts, which are never fused.
-template <int LAY>
+template <int LAY, bool GF = false>
 static hipError_t sweep_occupancy(int *per_cu, int kind, bool colscale) {
     constexpr bool S = LAY != kLaySorted && LAY != kLayRanges;
     if constexpr (!S) {
@@ -2181,9 +2253,9 @@ static hipError_t sweep_occupancy(int *per_cu, int kind, bool colscale) {
     }
     return kind == ECC_KIND_JACOBI
                ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                     per_cu, k_sweep<ECC_KIND_JACOBI, S, LAY>, kSweepThreads, 0)
+                     per_cu, k_sweep<ECC_KIND_JACOBI, S, LAY, false, GF>, kSweepThreads, 0)
                : hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                     per_cu, k_sweep<ECC_KIND_POWER, S, LAY>, kSweepThreads, 0);
+                     per_cu, k_sweep<ECC_KIND_POWER, S, LAY, false, GF>, kSweepThreads, 0);
 }
 
 template <int R, bool QUEUE, int FORM>
@@ -2243,7 +2315,7 @@ static bool merge_diag_values(int blocks, const unsigned long long *rep, const u
 // workgroup per CU fewer); constant diagonals ask here for the queue's kernel
 // that runs.
 static int32_t sweep_grid(int64_t n_items, int kind, int layout, int32_t short_r,
-                          bool colscale, int form) {
+                          bool colscale, int form, bool gather_first) {
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
@@ -2256,7 +2328,8 @@ static int32_t sweep_grid(int64_t n_items, int kind, int layout, int32_t short_r
                : form == kFormDiaConst ? short_occupancy<true, kFormDiaConst>(&per_cu, kind, short_r)
                : form == kFormDia      ? short_occupancy<false, kFormDia>(&per_cu, kind, short_r)
                                        : short_occupancy<false, kFormGeneral>(&per_cu, kind, short_r))
-            : sweep_occupancy<kLayStream>(&per_cu, kind, false);
+        : gather_first ? sweep_occupancy<kLayStream, true>(&per_cu, kind, false)
+                       : sweep_occupancy<kLayStream>(&per_cu, kind, false);
     if (e != hipSuccess || per_cu < 1) per_cu = 4;
     const int64_t resident = (int64_t)std::max(cus, 1) * per_cu;
     int64_t g = std::max<int64_t>(1, std::min<int64_t>({n_items, resident, (int64_t)kMaxSweepBlocks}));
@@ -2306,7 +2379,10 @@ static void launch_layout(ecc_matrix_t M, dim3 grid, dim3 block, hipStream_t st,
             else launch_short<K, S, false, kFormGeneral>(M, grid, block, st, a);
         }
     } else {
-        hipLaunchKernelGGL((k_sweep<K, S, kLayStream>), grid, block, 0, st, a);
+        if (M->gather_first)
+            hipLaunchKernelGGL((k_sweep<K, S, kLayStream, false, true>), grid, block, 0, st, a);
+        else
+            hipLaunchKernelGGL((k_sweep<K, S, kLayStream>), grid, block, 0, st, a);
     }
 }
 
@@ -2662,6 +2738,7 @@ static ecc_status_t ecc_matrix_create_impl(ecc_plan_t plan, const ecc_csr_t *A, 
     std::vector<int32_t> order, srp;
     RangeBuild RB;
     int64_t tile_plane = 0, tile_rows = 0, short_rows_total = 0;
+    bool gather_first = false;  // stream layout: products staged before the rows are summed
     // a small short-row problem is solved by one launch (tiny.hip)
     bool tiny = false;
     bool dia = false, dia_const = false;  // short layout in diagonal form, of constant diagonals
@@ -2808,6 +2885,29 @@ static ecc_status_t ecc_matrix_create_impl(ecc_plan_t plan, const ecc_csr_t *A, 
         }
     } else {
         build_items(rp, plan->counts, nullptr, items, fixups, n_pieces);
+        gather_first = A->nnz > 0 && !rows_alike(stream_shape(rp, items));
+        if (A->nnz > 0 && !gather_first) {
+            unsigned long long h_off = 0;
+            unsigned long long *d_off = nullptr;
+            hipError_t e = hipMalloc((void **)&d_off, sizeof(h_off));
+            if (e == hipSuccess) e = hipMemcpy(d_off, &h_off, sizeof(h_off), hipMemcpyHostToDevice);
+            if (e == hipSuccess) {
+                const int blocks = (int)std::min<int64_t>(4096, (n + 255) / 256);
+                hipLaunchKernelGGL(k_off_block, dim3(blocks), dim3(256), 0, plan->stream, n,
+                                   A->d_row_ptr, A->d_col, plan->P, plan->d_block_start, d_off);
+                e = hipGetLastError();
+                if (e == hipSuccess) e = hipStreamSynchronize(plan->stream);
+                if (e == hipSuccess)
+                    e = hipMemcpy(&h_off, d_off, sizeof(h_off), hipMemcpyDeviceToHost);
+            }
+            (void)hipFree(d_off);
+            if (e != hipSuccess) {
+                set_error("count of entries outside their row's block failed: %s",
+                          hipGetErrorString(e));
+                return e == hipErrorOutOfMemory ? ECC_ERR_ALLOC : ECC_ERR_DEVICE;
+            }
+            gather_first = (double)h_off >= kSumsOff * (double)A->nnz;
+        }
     }
     if ((int64_t)items.size() >= (int64_t(1) << 31)) {
         set_error("too many work items");
@@ -2832,7 +2932,8 @@ static ecc_status_t ecc_matrix_create_impl(ecc_plan_t plan, const ecc_csr_t *A, 
     M->tile_plane = tile_plane;
     M->tile_rows = tile_rows;
     M->grid = sweep_grid(M->n_items, kind, layout, M->short_r, colscale,
-                         dia ? kFormDia : kFormGeneral);
+                         dia ? kFormDia : kFormGeneral, gather_first);
+    M->gather_first = gather_first;
     M->dia = dia;
     M->dia_const = dia_const;
     M->dia_val = dia_val;
@@ -2860,7 +2961,7 @@ static ecc_status_t ecc_matrix_create_impl(ecc_plan_t plan, const ecc_csr_t *A, 
     M->pipe = M->queue && dia_const && dia_piped(kind, short_class(M->short_r), n_dia, dia_off);
     if (M->queue && dia_const)
         M->grid = sweep_grid(M->n_items, kind, layout, M->short_r, colscale,
-                             M->pipe ? kFormDiaPipe : kFormDiaConst);
+                             M->pipe ? kFormDiaPipe : kFormDiaConst, false);
     M->n_part = M->tiny ? n + 1 : M->queue ? M->n_items + 1 : (int64_t)M->grid + 1;
     auto fail = [&](const char *what) {
         set_error("%s", what);
@@ -3079,9 +3180,9 @@ ecc_status_t ecc_matrix_sweep(ecc_matrix_t M, int32_t *sweep, int32_t *workgroup
     ECC_ARG(M != nullptr, "matrix is NULL");
     ECC_ARG(sweep != nullptr, "NULL output");
     if (workgroups) *workgroups = M->grid;
-    *sweep = M->pipe                     ? ECC_SWEEP_PIPELINED
-             : M->layout == kLayStream ? ECC_SWEEP_GATHER_FIRST
-                                         : ECC_SWEEP_PLAIN;
+    *sweep = M->pipe           ? ECC_SWEEP_PIPELINED
+             : M->gather_first ? ECC_SWEEP_GATHER_FIRST
+                               : ECC_SWEEP_PLAIN;
     return ECC_OK;
 }
 

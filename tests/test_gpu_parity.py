@@ -650,6 +650,27 @@ def test_stream_rows_around_the_unroll(kind, lmin, lmax, n, P):
     _step_api_matches_solve((prob,))
 
 
+@pytest.mark.parametrize("kind,n,lmin,lmax,P,first", [
+    ("jacobi", 6000, 9, 10, 2, False), ("jacobi", 6000, 9, 10, 60, True),
+    ("jacobi", 6000, 14, 15, 1, True), ("jacobi", 6000, 18, 20, 1, False),
+    ("jacobi", 6000, 18, 20, 90, True), ("jacobi", 6000, 12, 48, 1, True),
+    ("jacobi", 2003, 12, 48, 400, True), ("power", 5003, 0, 33, 7, True),
+    ("power", 6000, 21, 22, 2, False), ("power", 6000, 25, 26, 2, True),
+    ("power", 6001, 21, 22, 60, True), ("power", 2049, 64, 64, 1, False)])
+def test_stream_rows_gathered_first(kind, n, lmin, lmax, P, first):
+    """Which stream rows are gathered before they are summed -- uneven rows,
+    long chains of gathers, many entries outside their rank's block -- and the
+    oracle's iterates in both orders, by the loop and by separate calls."""
+    E = _capi()
+    prob = _banded_problem(kind, n, lmin, lmax, P=P, T=12)
+    run = _iterative(prob)
+    got = E.ecc_matrix_sweep(run.mat)[0]
+    run.close()
+    assert got == (E.ECC_SWEEP_GATHER_FIRST if first else E.ECC_SWEEP_PLAIN)
+    _solve_and_compare(prob, bitwise=(lmax <= 16), layout="STREAM")
+    _step_api_matches_solve((prob,))
+
+
 @pytest.mark.parametrize("kind,lmin,lmax", [
     ("jacobi", 1, 2), ("power", 0, 3), ("jacobi", 2, 4), ("power", 3, 6), ("jacobi", 5, 7),
     ("jacobi", 8, 8), ("power", 1, 8)])
