@@ -417,6 +417,55 @@ static ecc_status_t launch_reduce_any(ReduceForm f, ReduceArgs &a, hipStream_t s
     return ECC_OK;
 }
 
+static ecc_status_t allreduce(ecc_plan_t plan, int64_t m, const double *const *d_fresh,
+                              double *const *d_slots, double *d_result, const uint8_t *d_arrived,
+                              uint8_t *d_eff_out, int32_t *d_result_clock, bool streamed) {
+    ecc_status_t st = check_plan(plan);
+    if (st != ECC_OK) return st;
+    ECC_ARG(m >= 0, "m must be >= 0");
+    ECC_ARG(d_fresh && d_slots, "d_fresh and d_slots must be device arrays of P pointers");
+    ECC_ARG(d_arrived != nullptr, "d_arrived is NULL");
+    ECC_ARG(d_result != nullptr || m == 0, "d_result is NULL");
+    const int64_t t = plan->clock;
+    ReduceArgs a{};
+    a.P = plan->P;
+    a.S = plan->S;
+    a.t = t;
+    a.arrived = d_arrived;
+    a.ver_in = plan->d_version + (t & 1) * plan->P;
+    a.ver_out = plan->d_version + ((t + 1) & 1) * plan->P;
+    a.age_state = plan->d_age;
+    a.eff_state = plan->d_eff;
+    a.forced = plan->d_forced;
+    a.eff_user = d_eff_out;
+    a.result_clock = d_result_clock;
+    a.m = m;
+    a.fresh = d_fresh;
+    a.slots = d_slots;
+    a.result = d_result;
+    ReduceForm form = reduce_form(a.P, m, d_fresh == (const double *const *)d_slots);
+    // whatever the length: the shapes below 2^32 threads that are not split
+    if (streamed && a.P >= kReduceManyRanks && m >= 2 && m < int64_t(1) << 32 &&
+        !kReduceShapes[form].split)
+        form = kReduceHeld;
+    if (reduce_grid(form, a.P, m) > 0x7fffffff) {
+        set_error("m too large");
+        return ECC_ERR_RANGE;
+    }
+    {
+        TimedLaunch timed(plan, ECC_TIMING_ALLREDUCE);
+        st = launch_reduce_any(form, a, plan->stream);
+    }
+    if (st != ECC_OK) return st;
+    plan->clock = t + 1;
+    return ECC_OK;
+}
+
+ecc_status_t allreduce_streamed(ecc_plan_t plan, int64_t m, double *const *d_slots,
+                                double *d_result, const uint8_t *d_arrived, uint8_t *d_eff_out) {
+    return allreduce(plan, m, d_slots, d_slots, d_result, d_arrived, d_eff_out, nullptr, true);
+}
+
 ecc_status_t launch_assemble(ecc_plan_t plan, const double *const *d_send,
                              const double *d_send_base, double *d_recv,
                              const uint8_t *d_arrived, uint8_t *d_eff_out, int32_t *d_age_out,
@@ -497,41 +546,8 @@ ecc_status_t ecc_allreduce_partial(ecc_plan_t plan, int64_t m, const double *con
                                    const uint8_t *d_arrived, uint8_t *d_eff_out,
                                    int32_t *d_result_clock) {
     clear_error();
-    ecc_status_t st = check_plan(plan);
-    if (st != ECC_OK) return st;
-    ECC_ARG(m >= 0, "m must be >= 0");
-    ECC_ARG(d_fresh && d_slots, "d_fresh and d_slots must be device arrays of P pointers");
-    ECC_ARG(d_arrived != nullptr, "d_arrived is NULL");
-    ECC_ARG(d_result != nullptr || m == 0, "d_result is NULL");
-    const int64_t t = plan->clock;
-    ReduceArgs a{};
-    a.P = plan->P;
-    a.S = plan->S;
-    a.t = t;
-    a.arrived = d_arrived;
-    a.ver_in = plan->d_version + (t & 1) * plan->P;
-    a.ver_out = plan->d_version + ((t + 1) & 1) * plan->P;
-    a.age_state = plan->d_age;
-    a.eff_state = plan->d_eff;
-    a.forced = plan->d_forced;
-    a.eff_user = d_eff_out;
-    a.result_clock = d_result_clock;
-    a.m = m;
-    a.fresh = d_fresh;
-    a.slots = d_slots;
-    a.result = d_result;
-    const ReduceForm form = reduce_form(a.P, m, d_fresh == (const double *const *)d_slots);
-    if (reduce_grid(form, a.P, m) > 0x7fffffff) {
-        set_error("m too large");
-        return ECC_ERR_RANGE;
-    }
-    {
-        TimedLaunch timed(plan, ECC_TIMING_ALLREDUCE);
-        st = launch_reduce_any(form, a, plan->stream);
-    }
-    if (st != ECC_OK) return st;
-    plan->clock = t + 1;
-    return ECC_OK;
+    return allreduce(plan, m, d_fresh, d_slots, d_result, d_arrived, d_eff_out, d_result_clock,
+                     false);
 }
 
 }  // extern "C"

@@ -478,6 +478,10 @@ ecc_status_t launch_assemble(ecc_plan_t plan, const double *const *d_send,
                              const double *d_send_base, double *d_recv,
                              const uint8_t *d_arrived, uint8_t *d_eff_out, int32_t *d_age_out,
                              const int32_t *d_done);
+// ecc_allreduce_partial of contributions held in their slots, read past the
+// caches at every length: for a caller whose other data should stay there.
+ecc_status_t allreduce_streamed(ecc_plan_t plan, int64_t m, double *const *d_slots,
+                                double *d_result, const uint8_t *d_arrived, uint8_t *d_eff_out);
 // One sweep launch.  With `arrived` non-NULL it is a whole loop iteration:
 // staleness decision, assembly of the arrived blocks into x_hat and the sweep
 // on the assembled view, on the plan's next clock.  Workgroup 0 also reduces

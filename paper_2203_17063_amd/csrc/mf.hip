@@ -16,7 +16,7 @@
 //      exactly one) also feed per-workgroup sums of e_k^2.  A worker taken
 //      at this clock writes its gradient into its slot, one not taken into
 //      its gradient buffer (its slot keeps its last taken gradient);
-//  (2) the partial allreduce of the workers' gradients (ecc_allreduce_partial:
+//  (2) the partial allreduce of the workers' gradients (ecc_allreduce_partial's:
 //      staleness decision, every gradient read from the slots in place);
 //  (3) k_mf_step: W := W - eta * (G * c_row + 2 lam W), c_row = K / (number
 //      of ratings of the row, at least 1); its workgroup 0 also reduces the
@@ -708,8 +708,11 @@ ecc_status_t ecc_mf_iterate(ecc_mf_t h, ecc_plan_t plan, double eta, double lam,
         ECC_LAUNCH_CHECK();
     }
     // every contribution is read from its slot: the taken ones were written
-    // there by the gradient kernel
-    st = ecc_allreduce_partial(plan, m, d_slots, d_slots, d_G, d_arrived, d_eff_out, nullptr);
+    // there by the gradient kernel.  Read past the caches, they leave there the
+    // model rows that the next iteration's gathers read (32 workers, us per
+    // iteration against the shapes of other held contributions: 121,132 rows
+    // of 4, 124 MB of slots, 99 / 112; 168,948 rows of 32, 1.4 GB, 651 / 710).
+    st = allreduce_streamed(plan, m, d_slots, d_G, d_arrived, d_eff_out);
     if (st != ECC_OK) return st;
     {
         TimedLaunch timed(plan, ECC_TIMING_MF_STEP);
