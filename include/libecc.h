@@ -193,7 +193,8 @@ ecc_status_t ecc_allgatherv_assemble_packed(ecc_plan_t plan, const double *d_sen
  *              d_slots[p]: the contribution was then written into the slot
  *              by its producer, which must do so only where eff[p] (the
  *              slot keeps the newest taken contribution), and the slot is
- *              read without being written.
+ *              read without being written.  Apart from that no slot may
+ *              overlap a contribution or another slot.
  *   d_result   device vector of m doubles; must not alias any slot or fresh.
  *   d_arrived, d_eff_out as for the assembly. */
 ecc_status_t ecc_allreduce_partial(ecc_plan_t plan, int64_t m, const double *const *d_fresh,
@@ -260,7 +261,10 @@ ecc_status_t ecc_allreduce_shape(int32_t P, int64_t m, int32_t held, int64_t *wo
  * ECC_LAYOUT_STREAM reads the matrix arrays at every sweep: they must then
  * outlive the handle and stay unchanged.  The other layouts sweep the copy
  * made here.  Two compact forms of the copy, reported by ecc_matrix_form,
- * leave the results bit for bit as the general form gives them:
+ * leave the iterates and assembled vectors bit for bit as the general form
+ * gives them (and the norms, but for rounding where more workgroups of a
+ * form's kernel fit on the device and the per-workgroup partial sums of
+ * ECC_SCHEDULE_STATIC then group the rows differently):
  * Diagonals (ECC_LAYOUT_SHORT): when every row's entries are in increasing
  * column order and lie on at most as many offsets col - row as the row class
  * R holds (a grid stencil: 3 offsets in 1-D, 5 in 2-D, 7 in 3-D), the copy

@@ -291,8 +291,8 @@ __global__ __launch_bounds__(kWideThreads) void k_allreduce_wide(
 // of 2.5M makes 306, and the 50 second ones cost a fifth).  Shorter vectors
 // take chunks of one pair per thread with more ranks in flight instead, and
 // the shortest the split form.  Measured on MI355X, us per call, 70 % of the
-// ranks arriving unless stated; "before" is a 1,024-thread workgroup of
-// 16,384 elements, one rank in flight, at every length:
+// ranks arriving and no bound on staleness; "before" is a 1,024-thread
+// workgroup of 16,384 elements, one rank in flight, at every length:
 //                  pairs  4,096  8,192  wide   before
 //   256 x 4,194,304 2,920  2,878  2,822  2,669  2,709
 //   256 x 2,500,000 1,756  1,811  2,077  1,717  1,765
@@ -314,6 +314,8 @@ __global__ __launch_bounds__(kWideThreads) void k_allreduce_wide(
 // 306 before; 32 x 3,520,000 (860 MiB) 359, 387, 390; 64 x 1,700,001 (830
 // MiB) 303, 329, 412; but 64 x 4,194,304 (2 GiB) 911, 863, 868; 128 x
 // 4,194,304 1,783, 1,669, 1,684; 128 x 150,001 (147 MiB) 57, 47, 277.
+// (The factorisation asks for this shape at every length, for what its loads
+// leave in the caches: allreduce_streamed.)
 constexpr int64_t kReduceCus = 256;
 constexpr int64_t kReduceFill = 200;        // workgroups that fill them well enough
 constexpr int32_t kReduceManyRanks = 16;    // wide chunks pay from here on
