@@ -960,7 +960,9 @@ def main():
                             "Infinity Fabric requests, Infinity Cache hits included)",
             "algorithmic_bytes_per_launch": res["dominant_bytes"],
             "algorithmic_model": "the method's data as its definition holds it (CSR for the "
-                                 "iterations), each element counted once",
+                                 "iterations), each element counted once; with a matrix in a "
+                                 "compact form value, hbm_peak_frac and frac are effective "
+                                 "rates on it, and frac_format is the share of the peak",
             "avg_launch_us": round(avg_dom_s * 1e6, 3),
             "launches_timed": dom_n,
             "timing": timing,
